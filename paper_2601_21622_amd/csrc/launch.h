@@ -79,11 +79,12 @@ struct VocabPlan {
   int tile_n;      // vocabulary columns per workgroup
   int ntiles;      // ceil(V / tile_n)
   int mtiles;      // workgroups along the hidden rows
-  int mblocks;     // bf16 row blocks per M-tile: of 16 rows (shallow), of 32 (deep)
+  int mblocks;     // row blocks per M-tile: of 16 rows (line schedule), of 32 (deep)
   int nbw;         // 16-entry vocabulary blocks per wave (bf16)
   int waves;       // waves per workgroup
   bool deep;       // bf16 deep-pipelined 32x32 schedule (more than 64 rows)
   bool packed;     // W in the fragment-order layout of launch_pack_vocab
+  bool lines;      // line schedule (float32, or bf16 with few rows)
 };
 VocabPlan vocab_plan(int dtype, int M, int K, int V, bool packed);
 size_t vocab_packed_bytes(int K, int V);
@@ -97,6 +98,14 @@ size_t vocab_workspace_bytes(const VocabPlan& p);
 hipError_t launch_vocab(int dtype, const VocabPlan& p, const void* hidden, const void* w,
                         float* logits, void* workspace, hipStream_t stream, hipEvent_t ev_start,
                         hipEvent_t ev_stop, int* clear = nullptr, int nclear = 0);
+constexpr int kLineMaxBlocks = 4;  // 16-row blocks per workgroup of the line schedule
+// The line schedule (lines.hip): a wave owns 16 vocabulary entries, a
+// workgroup p.mblocks 16-row blocks.  line_plan fills nbw, waves, mtiles and
+// mblocks for `blocks` 16-row blocks in all.
+void line_plan(int blocks, int V, VocabPlan* p);
+hipError_t launch_vocab_lines(bool f32, const VocabPlan& p, const void* hidden, const void* w, float* logits,
+                              float2* partials, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop,
+                              int* clear, int nclear);
 hipError_t launch_lse_combine(const VocabPlan& p, const float2* partials, float* row_lse,
                               hipStream_t stream);
 

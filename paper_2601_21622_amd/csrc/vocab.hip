@@ -7,14 +7,12 @@
 //
 // A workgroup owns a tile of vocabulary rows for all hidden rows of its
 // M-tile, so W (the dominant stream, K*V*2 bytes) is read from HBM once.
-// Every wave streams its own W fragments, either from the [V][K] layout or
-// from the fragment-ordered copy sd_pack_vocab makes at weight-load time (1 KB
+// Every wave streams its own W, either from the [V][K] layout or from the
+// fragment-ordered copy sd_pack_vocab makes at weight-load time (1 KB
 // contiguous per fragment).  The hidden rows, shared by every workgroup and
 // L2-resident, are staged per K-chunk in LDS in fragment order and read by
 // all waves.  Three schedules:
-//   * shallow (at most 64 hidden rows), MFMA 16x16x32: one 16-entry
-//     vocabulary block per wave, 256-wide K-chunks, one chunk of prefetch;
-//     several workgroups per CU keep enough W in flight.
+//   * line (float32, or at most 64 hidden rows): lines.hip.
 //   * deep (more rows), MFMA 32x32x16: the hidden rows are first repacked
 //     (pack_hidden_kernel) into 32-row fragments that LDS DMA moves 1 KB at a
 //     time; a workgroup's accumulators pin it to a CU.  Three shapes: four
@@ -39,238 +37,13 @@
 
 #include "common.h"
 #include "launch.h"
+#include "vocab_tile.h"
 
 namespace sdv {
 
 namespace {
 
 constexpr int kVThreads = 256;
-
-// Counters a later launch on the stream expects at zero (the acceptance's
-// arrival counters): cleared by the first workgroup of a vocabulary launch.
-__device__ __forceinline__ void clear_counters(int* __restrict__ clear, int nclear) {
-  if (blockIdx.x == 0 && blockIdx.y == 0)
-    for (int i = threadIdx.x; i < nclear; i += blockDim.x) clear[i] = 0;
-}
-constexpr int kTileN = 64;  // vocabulary rows per workgroup (4 waves x 16)
-
-// Epilogue of one workgroup of WM x WN waves.  Wave (wm, wn) = (wave / WN,
-// wave % WN) holds in acc[mb][nb] hidden row m0 + r0 + mb*16 + (lane & 15),
-// with r0 = wm*MBW*16, and vocabulary entries (blk0 + nb)*16 + (lane>>4)*4
-// .. +3, where blk0 is the wave's first 16-entry block.  Writes the logits,
-// then the tile's per-row maximum and sum of exponentials, combined over the
-// WN waves that share the rows through `red` ([WN][WM*MBW*16] floats).
-template <int MBW, int NBW, int WM, int WN>
-__device__ __forceinline__ void tile_epilogue(const f32x4 (&acc)[MBW][NBW], int M, int V, int ntiles, int tile,
-                                              int m0, int blk0, float* __restrict__ logits,
-                                              float2* __restrict__ partials, float (*red)[WM * MBW * 16]) {
-  const int wave = threadIdx.x >> 6;
-  const int wn = wave % WN;
-  const int r0 = (wave / WN) * MBW * 16;
-  const int lane = threadIdx.x & 63;
-  const int lr = lane & 15;
-  const int lg = lane >> 4;
-  const bool v4 = (V % 4) == 0;
-  float tmax[MBW];
-#pragma unroll
-  for (int mb = 0; mb < MBW; ++mb) {
-    const int m = m0 + r0 + mb * 16 + lr;
-    float x = -INFINITY;
-#pragma unroll
-    for (int nb = 0; nb < NBW; ++nb) {
-      const int v0 = (blk0 + nb) * 16 + lg * 4;
-      if (m < M) {
-        float* dst = logits + (int64_t)m * V + v0;
-        if (v4 && v0 + 3 < V) {
-          *reinterpret_cast<f32x4*>(dst) = acc[mb][nb];
-        } else {
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            if (v0 + i < V) dst[i] = acc[mb][nb][i];
-        }
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) x = (v0 + i < V) ? fmaxf(x, acc[mb][nb][i]) : x;
-    }
-    x = fmaxf(x, __shfl_xor(x, 16));
-    x = fmaxf(x, __shfl_xor(x, 32));
-    if (lg == 0) red[wn][r0 + mb * 16 + lr] = x;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int mb = 0; mb < MBW; ++mb) {
-    const int r = r0 + mb * 16 + lr;
-    float x = red[0][r];
-#pragma unroll
-    for (int w = 1; w < WN; ++w) x = fmaxf(x, red[w][r]);
-    tmax[mb] = x;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int mb = 0; mb < MBW; ++mb) {
-    float sm = 0.f;
-#pragma unroll
-    for (int nb = 0; nb < NBW; ++nb) {
-      const int v0 = (blk0 + nb) * 16 + lg * 4;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) sm += (v0 + i < V) ? expf(acc[mb][nb][i] - tmax[mb]) : 0.f;
-    }
-    sm += __shfl_xor(sm, 16);
-    sm += __shfl_xor(sm, 32);
-    if (lg == 0) red[wn][r0 + mb * 16 + lr] = sm;
-  }
-  __syncthreads();
-  if (wn == 0 && lg == 0) {
-#pragma unroll
-    for (int mb = 0; mb < MBW; ++mb) {
-      const int r = r0 + mb * 16 + lr;
-      const int m = m0 + r;
-      if (m < M) {
-        float sm;
-        if (WN == 8)
-          sm = ((red[0][r] + red[1][r]) + (red[2][r] + red[3][r])) + ((red[4][r] + red[5][r]) + (red[6][r] + red[7][r]));
-        else if (WN == 4)
-          sm = (red[0][r] + red[1][r]) + (red[2][r] + red[3][r]);
-        else if (WN == 2)
-          sm = red[0][r] + red[1][r];
-        else
-          sm = red[0][r];
-        partials[(int64_t)m * ntiles + tile] = make_float2(tmax[mb], sm);
-      }
-    }
-  }
-}
-
-// Shallow schedule: waves per workgroup.  Every wave of a workgroup multiplies
-// the same hidden chunk; eight waves halve the L2 requests that stage it but
-// measured slower than four (half as many workgroups in flight per CU).
-constexpr int kShallowWaves = 4;
-
-template <int MB, int KC, int NW>
-struct VocabCfg {
-  static constexpr int kThreads = NW * kWave;
-  static constexpr int kSteps = KC / 32;                  // MFMA k-steps per chunk
-  static constexpr int kFragBytes = 1024;                 // one 16x32 bf16 fragment
-  static constexpr int kBufBytes = MB * kSteps * kFragBytes;
-  static constexpr int kPieces = 16 * MB * KC / 8;        // 16-byte pieces per A chunk
-  static constexpr int kPiecesPerThread = (kPieces + kThreads - 1) / kThreads;
-};
-
-// LDS slot (16 bytes) of lane s of hidden fragment ks in the shallow
-// schedule's chunk buffer: the lane holds row s % 16 and k piece g = s / 16;
-// the low four bits of the slot are XORed with 2g + (ks & 1) + 8 ((ks >> 1) &
-// 1).  Consecutive threads store consecutive 16-byte pieces of one row (g
-// fastest, then ks); without the XOR every store of a row lands on the same
-// bank group.  With it, any 8 consecutive stores, and any 8 consecutive
-// lanes' reads, cover 8 distinct 16-byte slots of a 128-byte span.
-__device__ __forceinline__ int shallow_slot(int s, int ks) {
-  const int t = 8 * ((ks >> 1) & 1) + 2 * ((s >> 4) & 3) + (ks & 1);
-  return (s & 48) | ((s & 15) ^ t);
-}
-
-template <int MB, int KC, int NW, bool PACKED>
-__global__ __launch_bounds__(NW * kWave)
-void vocab_bf16_kernel(int M, int K, int V, int ntiles, const uint16_t* __restrict__ hidden,
-                       const uint16_t* __restrict__ w, float* __restrict__ logits,
-                       float2* __restrict__ partials, int* __restrict__ clear, int nclear) {
-  using C = VocabCfg<MB, KC, NW>;
-  clear_counters(clear, nclear);
-  __shared__ __align__(16) unsigned char abuf[2][C::kBufBytes];
-  __shared__ float red[NW][16 * MB];
-
-  const int tile = blockIdx.x;
-  const int m0 = blockIdx.y * 16 * MB;
-  const int wave = threadIdx.x >> 6;
-  const int lane = threadIdx.x & 63;
-  const int lr = lane & 15;
-  const int lg = lane >> 4;
-  // W fragment stream of this wave: 16 vocabulary rows (clamped; masked in the
-  // epilogue).  Row-major: the lane's row from column lg*8.  Packed: fragment
-  // (k-step s, block) at ((s * nblk + block) * 64 + lane) * 8.
-  const int nblk = (V + 15) / 16;
-  const uint16_t* wrow;
-  int64_t wstep;  // elements between consecutive k-steps
-  if (PACKED) {
-    wrow = w + ((int64_t)min(nblk - 1, tile * NW + wave) * 64 + lane) * 8;
-    wstep = (int64_t)nblk * 64 * 8;
-  } else {
-    wrow = w + (int64_t)min(V - 1, (tile * NW + wave) * 16 + lr) * K + lg * 8;
-    wstep = 32;
-  }
-  const int nchunks = K / KC;
-
-  // Cooperative A-chunk load: piece p -> (row, 16-byte k piece), coalesced along k.
-  u32x4 areg[C::kPiecesPerThread];
-  auto load_a = [&](int kc) {
-#pragma unroll
-    for (int i = 0; i < C::kPiecesPerThread; ++i) {
-      const int p = threadIdx.x + i * C::kThreads;
-      const int row = p / (KC / 8);
-      const int kp = p - row * (KC / 8);
-      u32x4 v = {0u, 0u, 0u, 0u};
-      if (p < C::kPieces && m0 + row < M)
-        v = *reinterpret_cast<const u32x4*>(hidden + (int64_t)(m0 + row) * K + kc * KC + kp * 8);
-      areg[i] = v;
-    }
-  };
-  auto store_a = [&](int buf) {
-#pragma unroll
-    for (int i = 0; i < C::kPiecesPerThread; ++i) {
-      const int p = threadIdx.x + i * C::kThreads;
-      if (p < C::kPieces) {
-        const int row = p / (KC / 8);
-        const int kp = p - row * (KC / 8);
-        const int mb = row >> 4, r = row & 15, ks = kp >> 2, g = kp & 3;
-        const int slot = (mb * C::kSteps + ks) * 64 + shallow_slot(r + 16 * g, ks);
-        *reinterpret_cast<u32x4*>(abuf[buf] + slot * 16) = areg[i];
-      }
-    }
-  };
-
-  // W is read once per launch: the nontemporal hint keeps it from displacing
-  // the hidden rows, which every workgroup re-reads from L2 (5.4 -> 5.9 TB/s
-  // measured at 48 x 4096 x 32000).
-  bf16x8 wcur[C::kSteps], wnext[C::kSteps];
-  auto load_w = [&](bf16x8* dst, int kc) {
-#pragma unroll
-    for (int ks = 0; ks < C::kSteps; ++ks)
-      dst[ks] = load_bf16x8_stream(wrow + (int64_t)(kc * C::kSteps + ks) * wstep);
-  };
-
-  f32x4 acc[MB][1];
-#pragma unroll
-  for (int mb = 0; mb < MB; ++mb) acc[mb][0] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  load_a(0);
-  load_w(wcur, 0);
-  store_a(0);
-  lds_barrier();
-  for (int kc = 0; kc < nchunks; ++kc) {
-    const int buf = kc & 1;
-    const bool more = kc + 1 < nchunks;
-    if (more) {
-      load_a(kc + 1);
-      load_w(wnext, kc + 1);
-    }
-#pragma unroll
-    for (int ks = 0; ks < C::kSteps; ++ks) {
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb) {
-        const bf16x8 a = __builtin_bit_cast(
-            bf16x8, *reinterpret_cast<const u32x4*>(abuf[buf] + ((mb * C::kSteps + ks) * 64 + shallow_slot(lane, ks)) * 16));
-        acc[mb][0] = mfma16x16x32(wcur[ks], a, acc[mb][0]);
-      }
-    }
-    if (more) {
-      store_a(buf ^ 1);
-#pragma unroll
-      for (int ks = 0; ks < C::kSteps; ++ks) wcur[ks] = wnext[ks];
-    }
-    lds_barrier();
-  }
-
-  tile_epilogue<MB, 1, 1, NW>(acc, M, V, ntiles, tile, m0, tile * NW + wave, logits, partials, red);
-}
 
 // Deep schedule (more than 64 rows) on MFMA 32x32x16: the accumulators of up
 // to 384 rows pin one workgroup of four waves to a CU, and a single wave per
@@ -928,54 +701,6 @@ void pack_hidden_kernel(int M, int K, const uint16_t* __restrict__ hidden, uint1
   }
 }
 
-// float32 path: 64 rows x 64 vocabulary entries per workgroup, LDS-tiled FMA.
-constexpr int kF32KC = 32;
-__global__ __launch_bounds__(kVThreads)
-void vocab_f32_kernel(int M, int K, int V, int ntiles, const float* __restrict__ hidden,
-                      const float* __restrict__ w, float* __restrict__ logits,
-                      float2* __restrict__ partials, int* __restrict__ clear, int nclear) {
-  clear_counters(clear, nclear);
-  __shared__ float wt[kF32KC][kTileN + 1];  // [k][vocab]
-  __shared__ float ht[64][kF32KC + 1];      // [row][k]
-  const int tile = blockIdx.x;
-  const int m0 = blockIdx.y * 64;
-  const int col = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const int v = tile * kTileN + col;
-  float acc[16];
-#pragma unroll
-  for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-  for (int k0 = 0; k0 < K; k0 += kF32KC) {
-    for (int i = threadIdx.x; i < kTileN * kF32KC; i += kVThreads) {
-      const int r = i / kF32KC, k = i - r * kF32KC;
-      const int vv = min(V - 1, tile * kTileN + r);
-      wt[k][r] = (k0 + k < K) ? w[(int64_t)vv * K + k0 + k] : 0.f;
-    }
-    for (int i = threadIdx.x; i < 64 * kF32KC; i += kVThreads) {
-      const int r = i / kF32KC, k = i - r * kF32KC;
-      ht[r][k] = (m0 + r < M && k0 + k < K) ? hidden[(int64_t)(m0 + r) * K + k0 + k] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll 4
-    for (int k = 0; k < kF32KC; ++k) {
-      const float wv = wt[k][col];
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[i] = fmaf(ht[wave + 4 * i][k], wv, acc[i]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int m = m0 + wave + 4 * i;
-    if (m >= M) continue;  // uniform across the wave
-    if (v < V) logits[(int64_t)m * V + v] = acc[i];
-    const float x = v < V ? acc[i] : -INFINITY;
-    const float mx = wave_max(x);
-    const float s = wave_sum(v < V ? expf(x - mx) : 0.f);
-    if (col == 0) partials[(int64_t)m * ntiles + tile] = make_float2(mx, s);
-  }
-}
-
 // One wave per row: maximum over tiles, then a float64 sum of the rescaled tile sums.
 __global__ __launch_bounds__(kVThreads)
 void lse_combine_kernel(int M, int ntiles, const float2* __restrict__ partials, float* __restrict__ row_lse) {
@@ -1002,28 +727,6 @@ void pack_vocab_kernel(int K, int V, const uint16_t* __restrict__ w, uint16_t* _
     if (row < V) v = *reinterpret_cast<const u32x4*>(w + (int64_t)row * K + s * 32 + (lane >> 4) * 8);
     *reinterpret_cast<u32x4*>(out + i * 8) = v;
   }
-}
-
-template <int MB, int KC>
-hipError_t launch_shallow(const VocabPlan& p, const void* hidden, const void* w, float* logits, float2* partials,
-                          hipStream_t stream, hipEvent_t e0, hipEvent_t e1, int* clear, int nclear) {
-  const dim3 grid(p.ntiles, p.mtiles), block(kShallowWaves * kWave);
-  const uint16_t* h = static_cast<const uint16_t*>(hidden);
-  const uint16_t* wv = static_cast<const uint16_t*>(w);
-  if (p.packed)
-    hipExtLaunchKernelGGL((vocab_bf16_kernel<MB, KC, kShallowWaves, true>), grid, block, 0, stream, e0, e1, 0, p.M,
-                          p.K, p.V, p.ntiles, h, wv, logits, partials, clear, nclear);
-  else
-    hipExtLaunchKernelGGL((vocab_bf16_kernel<MB, KC, kShallowWaves, false>), grid, block, 0, stream, e0, e1, 0, p.M,
-                          p.K, p.V, p.ntiles, h, wv, logits, partials, clear, nclear);
-  return hipGetLastError();
-}
-
-template <int MB>
-hipError_t launch_shallow_mb(const VocabPlan& p, const void* hidden, const void* w, float* logits, float2* partials,
-                             hipStream_t stream, hipEvent_t e0, hipEvent_t e1, int* clear, int nclear) {
-  if (p.K % 256 == 0) return launch_shallow<MB, 256>(p, hidden, w, logits, partials, stream, e0, e1, clear, nclear);
-  return launch_shallow<MB, 32>(p, hidden, w, logits, partials, stream, e0, e1, clear, nclear);
 }
 
 template <int MB, int NB, int NW, int S = (NW == 8 ? 3 : 6)>
@@ -1074,7 +777,6 @@ struct DeepShape {
   int nb, nw, cap;
 };
 constexpr DeepShape kDeepShapes[4] = {{1, 4, 12}, {2, 4, 7}, {2, 8, 5}, {kWideNB, 4, kWideMaxMB}};
-constexpr int kShallowMaxBlocks = 4;  // 16-row blocks of the shallow schedule
 
 // Per-CU cost of a deep plan in the inflow model of the deep kernel: the
 // workgroups a CU runs one after another (CUs of the MI355X: 256), each
@@ -1112,22 +814,15 @@ hipError_t launch_pack_vocab(int K, int V, const void* w, void* out, hipStream_t
 VocabPlan vocab_plan(int dtype, int M, int K, int V, bool packed) {
   VocabPlan p;
   p.packed = packed;
+  p.lines = false;
   p.M = M;
   p.K = K;
   p.V = V;
   const int blocks = (M + 15) / 16;
-  if (dtype == 0) {
+  if (dtype == 0 || blocks <= kLineMaxBlocks) {
     p.deep = false;
-    p.mblocks = 4;
-    p.nbw = 1;
-    p.waves = 4;
-    p.mtiles = (M + 63) / 64;
-  } else if (blocks <= kShallowMaxBlocks) {
-    p.deep = false;
-    p.mblocks = blocks;
-    p.nbw = kShallowWaves / 4;  // a 16-entry block per wave
-    p.waves = 4;
-    p.mtiles = 1;
+    p.lines = true;
+    line_plan(blocks, V, &p);
   } else {
     // The deep shape the inflow model prices lowest (ties go to the
     // narrower tile).
@@ -1170,21 +865,8 @@ hipError_t launch_vocab(int dtype, const VocabPlan& p, const void* hidden, const
   if (clear == nullptr) nclear = 0;
   float2* partials = static_cast<float2*>(workspace);
   uint16_t* hpacked = reinterpret_cast<uint16_t*>(static_cast<char*>(workspace) + partial_bytes(p));
-  if (dtype == 0) {
-    hipExtLaunchKernelGGL(vocab_f32_kernel, dim3(p.ntiles, p.mtiles), dim3(kVThreads), 0, stream, e0, e1, 0, p.M, p.K,
-                          p.V, p.ntiles, static_cast<const float*>(hidden), static_cast<const float*>(w), logits,
-                          partials, clear, nclear);
-    return hipGetLastError();
-  }
-  if (!p.deep) {
-    switch (p.mblocks) {
-      case 1: return launch_shallow_mb<1>(p, hidden, w, logits, partials, stream, e0, e1, clear, nclear);
-      case 2: return launch_shallow_mb<2>(p, hidden, w, logits, partials, stream, e0, e1, clear, nclear);
-      case 3: return launch_shallow_mb<3>(p, hidden, w, logits, partials, stream, e0, e1, clear, nclear);
-      case 4: return launch_shallow_mb<4>(p, hidden, w, logits, partials, stream, e0, e1, clear, nclear);
-      default: return hipErrorInvalidValue;
-    }
-  }
+  if (p.lines)
+    return launch_vocab_lines(dtype == 0, p, hidden, w, logits, partials, stream, e0, e1, clear, nclear);
 #define SDV_D(B, N, W) \
   case B: return launch_deep<B, N, W>(p, hidden, w, logits, partials, hpacked, stream, e0, e1, clear, nclear);
   if (p.nbw == 2 * kWideNB) {

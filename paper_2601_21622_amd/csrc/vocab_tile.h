@@ -1,0 +1,105 @@
+// Parts shared by the vocabulary projection's schedules (gfx950).
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "common.h"
+
+namespace sdv {
+
+// Counters a later launch on the stream expects at zero (the acceptance's
+// arrival counters): cleared by the first workgroup of a vocabulary launch.
+__device__ __forceinline__ void clear_counters(int* __restrict__ clear, int nclear) {
+  if (blockIdx.x == 0 && blockIdx.y == 0)
+    for (int i = threadIdx.x; i < nclear; i += blockDim.x) clear[i] = 0;
+}
+
+// Epilogue of one workgroup of WM x WN waves.  Wave (wm, wn) = (wave / WN,
+// wave % WN) holds in acc[mb][nb] hidden row m0 + r0 + mb*16 + (lane & 15),
+// with r0 = wm*MBW*16, and vocabulary entries (blk0 + nb)*16 + (lane>>4)*4
+// .. +3, where blk0 is the wave's first 16-entry block.  Writes the logits,
+// then the tile's per-row maximum and sum of exponentials, combined over the
+// WN waves that share the rows through `red` ([WN][WM*MBW*16] floats).
+template <int MBW, int NBW, int WM, int WN>
+__device__ __forceinline__ void tile_epilogue(const f32x4 (&acc)[MBW][NBW], int M, int V, int ntiles, int tile,
+                                              int m0, int blk0, float* __restrict__ logits,
+                                              float2* __restrict__ partials, float (*red)[WM * MBW * 16]) {
+  const int wave = threadIdx.x >> 6;
+  const int wn = wave % WN;
+  const int r0 = (wave / WN) * MBW * 16;
+  const int lane = threadIdx.x & 63;
+  const int lr = lane & 15;
+  const int lg = lane >> 4;
+  const bool v4 = (V % 4) == 0;
+  float tmax[MBW];
+#pragma unroll
+  for (int mb = 0; mb < MBW; ++mb) {
+    const int m = m0 + r0 + mb * 16 + lr;
+    float x = -INFINITY;
+#pragma unroll
+    for (int nb = 0; nb < NBW; ++nb) {
+      const int v0 = (blk0 + nb) * 16 + lg * 4;
+      if (m < M) {
+        float* dst = logits + (int64_t)m * V + v0;
+        if (v4 && v0 + 3 < V) {
+          *reinterpret_cast<f32x4*>(dst) = acc[mb][nb];
+        } else {
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (v0 + i < V) dst[i] = acc[mb][nb][i];
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x = (v0 + i < V) ? fmaxf(x, acc[mb][nb][i]) : x;
+    }
+    x = fmaxf(x, __shfl_xor(x, 16));
+    x = fmaxf(x, __shfl_xor(x, 32));
+    if (lg == 0) red[wn][r0 + mb * 16 + lr] = x;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int mb = 0; mb < MBW; ++mb) {
+    const int r = r0 + mb * 16 + lr;
+    float x = red[0][r];
+#pragma unroll
+    for (int w = 1; w < WN; ++w) x = fmaxf(x, red[w][r]);
+    tmax[mb] = x;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int mb = 0; mb < MBW; ++mb) {
+    float sm = 0.f;
+#pragma unroll
+    for (int nb = 0; nb < NBW; ++nb) {
+      const int v0 = (blk0 + nb) * 16 + lg * 4;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) sm += (v0 + i < V) ? expf(acc[mb][nb][i] - tmax[mb]) : 0.f;
+    }
+    sm += __shfl_xor(sm, 16);
+    sm += __shfl_xor(sm, 32);
+    if (lg == 0) red[wn][r0 + mb * 16 + lr] = sm;
+  }
+  __syncthreads();
+  if (wn == 0 && lg == 0) {
+#pragma unroll
+    for (int mb = 0; mb < MBW; ++mb) {
+      const int r = r0 + mb * 16 + lr;
+      const int m = m0 + r;
+      if (m < M) {
+        float sm;
+        if (WN == 8)
+          sm = ((red[0][r] + red[1][r]) + (red[2][r] + red[3][r])) + ((red[4][r] + red[5][r]) + (red[6][r] + red[7][r]));
+        else if (WN == 4)
+          sm = (red[0][r] + red[1][r]) + (red[2][r] + red[3][r]);
+        else if (WN == 2)
+          sm = red[0][r] + red[1][r];
+        else
+          sm = red[0][r];
+        partials[(int64_t)m * ntiles + tile] = make_float2(tmax[mb], sm);
+      }
+    }
+  }
+}
+
+}  // namespace sdv

@@ -1,0 +1,59 @@
+"""GPU parity of the projection's line schedule (float32, and bfloat16 with at
+most 64 rows): every row-block count, two, four and eight waves per workgroup
+(chosen from the vocabulary), M-tiles of float32 past 64 rows, rows and
+vocabularies off every tile, K from one half line (bfloat16: 32 entries) past
+the pipeline's depth, odd numbers of half lines, row-major and packed weights.
+
+Bound: a float32 sum of K products in any order is within K * 2^-24 * sum
+|h||w| of the exact one (products of float32 inputs add one rounding each;
+those of bfloat16 are exact)."""
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2601_21622_amd as sd
+
+from gpu_util import announce
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # dtype, rows (batch, positions), K, V, packed
+    ("f32", (1, 2), 32, 1, False), ("f32", (3, 5), 64, 33, False), ("f32", (4, 4), 96, 15, False),
+    ("f32", (1, 17), 320, 3001, False), ("f32", (8, 6), 544, 12301, False), ("f32", (13, 5), 160, 24700, False),
+    ("f32", (26, 5), 288, 129, False), ("f32", (16, 4), 1024, 25000, False),
+    ("bf16", (1, 2), 32, 17, False), ("bf16", (1, 2), 32, 17, True), ("bf16", (4, 4), 64, 1, True),
+    ("bf16", (1, 17), 96, 3001, False), ("bf16", (1, 17), 96, 3001, True), ("bf16", (8, 6), 352, 12301, False),
+    ("bf16", (8, 6), 352, 12301, True), ("bf16", (7, 7), 1312, 24700, False), ("bf16", (7, 7), 1312, 24700, True),
+    ("bf16", (16, 4), 1504, 24703, False), ("bf16", (16, 4), 512, 65, True),
+]
+
+
+@pytest.mark.parametrize("dtype,rows,K,V,packed", CASES)
+def test_line_schedule_within_rounding_bound(dtype, rows, K, V, packed):
+    (B, G), M = rows, rows[0] * rows[1]
+    announce(f"line schedule dtype={dtype} M={M} K={K} V={V} packed={packed}")
+    g = torch.Generator().manual_seed(M * 1000003 + K * 101 + V)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    h, w = torch.randn(M, K, generator=g).to(dt), (torch.randn(V, K, generator=g) / K ** 0.5).to(dt)
+    dims = sd.Dims(B, G - 1, 1, 1, 64, K, V, sd.SD_DTYPE_F32 if dtype == "f32" else sd.SD_DTYPE_BF16,
+                   sd.SD_FLAG_PACKED_VOCAB if packed else 0)
+    wd = w.cuda()
+    if packed:
+        wp = torch.empty(sd.sd_vocab_packed_bytes(dims) // 2, dtype=dt, device="cuda")
+        sd.sd_pack_vocab(dims, wd, wp)
+        wd = wp
+    logits = torch.full((M, V), float("nan"), device="cuda")
+    lse = torch.full((M,), float("nan"), device="cuda")
+    ws = torch.full((sd.sd_workspace_bytes(dims, G),), 0xA5, dtype=torch.uint8, device="cuda")
+    sd.sd_verify_logits(dims, h.cuda(), wd, logits, lse, ws)
+    hd, wdd = h.double().numpy(), w.double().numpy()
+    ref = hd @ wdd.T
+    bound = K * 2.0 ** -24 * (np.abs(hd) @ np.abs(wdd).T) + 1e-30
+    got = logits.cpu().double().numpy()
+    assert np.all(np.abs(got - ref) <= bound), float(np.max(np.abs(got - ref) / bound))
+    mx = got.max(axis=1, keepdims=True)
+    want = (mx + np.log(np.exp(got - mx).sum(axis=1, keepdims=True)))[:, 0]
+    # exp and the tile sums in float32, the fold in float64, the result rounded to float32
+    assert np.all(np.abs(lse.cpu().double().numpy() - want) <= 1e-5 * np.maximum(1.0, np.abs(want)))
