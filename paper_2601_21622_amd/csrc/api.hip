@@ -547,31 +547,38 @@ int sd_verify_step_sampled(const sd_dims_t* dims, const sd_sampling_t* sampling,
   if (st != SD_OK) return st;
   st = check_kv(dims, kv_off, kv_len);
   if (st != SD_OK) return st;
-  const AttnShape s = attn_shape(dims, scale, kv_len);
-  const size_t need = std::max(attention_ws(dims, total_chunks(kv_len, dims->batch, s.chunk_keys)),
-                               logits_ws(dims) + accept_stage_ws(dims));
-  if (workspace_bytes < need) return SD_ERR_WORKSPACE;
+  // As in the chain step the attention merge rides in the acceptance launch,
+  // its partials in a region of their own; a workspace that only holds the
+  // stages one after another gets the merge as a launch of its own.
+  const size_t attn_bytes = step_attention_ws(dims, kv_len, scale, nullptr);
+  const size_t rest = logits_ws(dims) + accept_stage_ws(dims);
+  if (workspace_bytes < std::max(attn_bytes, rest)) return SD_ERR_WORKSPACE;
+  const bool defer = hidden != nullptr && workspace_bytes >= attn_bytes + rest;
 
   hipEvent_t ev[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
   if (kernel_events != nullptr)
     for (int i = 0; i < 6; ++i) ev[i] = static_cast<hipEvent_t>(kernel_events[i]);
   hipStream_t stm = static_cast<hipStream_t>(stream);
-  st = run_attention(dims, q, k_pool, v_pool, kv_off, kv_len, scale, attn_out, workspace, stm, ev[0], ev[1]);
+  std::vector<CombineJob> merges;
+  st = run_attention(dims, q, k_pool, v_pool, kv_off, kv_len, scale, attn_out, workspace, stm, ev[0], ev[1], nullptr,
+                     nullptr, defer ? &merges : nullptr);
   if (st != SD_OK) return st;
   const VocabPlan vp = vocab_plan(dims->dtype, dims->batch * (dims->gamma + 1), dims->hidden, dims->vocab,
                                   (dims->flags & SD_FLAG_PACKED_VOCAB) != 0);
   // The projection launch clears the acceptance's arrival counters, so the
   // acceptance runs as one launch.
-  void* acc_ws = static_cast<char*>(workspace) + logits_ws(dims);
-  if (launch_vocab(dims->dtype, vp, hidden != nullptr ? hidden : attn_out, w_vocab, logits, workspace, stm, ev[2],
+  void* vws = static_cast<char*>(workspace) + (defer ? attn_bytes : 0);
+  void* acc_ws = static_cast<char*>(vws) + logits_ws(dims);
+  if (launch_vocab(dims->dtype, vp, hidden != nullptr ? hidden : attn_out, w_vocab, logits, vws, stm, ev[2],
                    ev[3], accept_arrivals(acc_ws, dims->batch, dims->vocab), dims->batch) != hipSuccess)
     return SD_ERR_HIP;
   WarpRow* warp = reinterpret_cast<WarpRow*>(static_cast<char*>(acc_ws) + accept_ws(dims));
   if (launch_warp(dims->batch * (dims->gamma + 1), dims->vocab, logits, sampling->temperature, sampling->top_k,
-                  sampling->top_p, warp, row_lse, row_min_logit, stm, ev[4]) != hipSuccess)
+                  sampling->top_p, warp, row_lse, row_min_logit, stm, ev[4], static_cast<const float2*>(vws), vp.ntiles,
+                  vp.tile_n) != hipSuccess)
     return SD_ERR_HIP;
   return run_accept(dims, logits, nullptr, nullptr, 0, q_draft, draft_tok, u, kv_len, accept_len, out_tok,
-                    new_kv_len, acc_ws, stm, nullptr, ev[5], warp, nullptr, true);
+                    new_kv_len, acc_ws, stm, nullptr, ev[5], warp, defer ? &merges : nullptr, true);
 }
 
 int sd_accept_tree(const sd_dims_t* dims, const float* logits_or_probs, const float* row_lse, const int32_t* tokens,

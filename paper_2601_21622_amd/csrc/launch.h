@@ -121,9 +121,11 @@ struct WarpRow {
 // temperature 0 selects greedy; top_k 0 or >= V and top_p >= 1 switch the cuts off.
 // Also writes each row's normaliser and smallest kept logit (-inf: no cut,
 // +inf: greedy) to row_lse / row_min_logit.  ev_start (may be null) is
-// recorded as the kernel starts.
+// recorded as the kernel starts.  With `partials` (the projection's [M][ntiles]
+// statistics of tile_n consecutive entries each) the row maxima come from them.
 hipError_t launch_warp(int M, int V, const float* logits, float temperature, int top_k, float top_p, WarpRow* out,
-                       float* row_lse, float* row_min_logit, hipStream_t stream, hipEvent_t ev_start);
+                       float* row_lse, float* row_min_logit, hipStream_t stream, hipEvent_t ev_start,
+                       const float2* partials = nullptr, int ntiles = 0, int tile_n = 0);
 
 // Acceptance and resampling.
 struct AcceptBatch {

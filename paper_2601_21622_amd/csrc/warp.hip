@@ -10,25 +10,36 @@
 //   p'(v) = [key(v) >= theta] exp(logit(v) / T - lse)   (greedy: [v == argmax]).
 //
 // One workgroup of 1024 threads per row:
-//   1. the largest logit and the first index holding it (one pass);
-//   2. top-k: a radix descent over the 32-bit order keys of the logits, 11, 11
-//      and 10 bits per level, with per-bucket counts and masses in LDS; the
-//      bucket where the running count from the top reaches k holds the cut;
-//   3. top-p: the same descent over the kept tokens, on masses, against
-//      ceil(top_p * kept mass) (with no top-k cut, the kept mass is the
-//      total of the first level's histogram, which holds every entry);
+//   1. the largest logit (greedy: and the first index holding it), from one
+//      pass, or in a step from the projection's tile maxima (greedy then reads
+//      only the tiles that reach it);
+//   2. a pass that keeps the few thousand largest entries in LDS and, with no
+//      top-k cut, sums the row's mass; with a top-k cut and tile maxima only
+//      tiles that reach the bound are read;
+//   3. the cut among the kept entries: a wave sort for top-k up to 64, else a
+//      radix descent on counts (top-k) or masses against ceil(top_p * kept
+//      mass).  Rows whose cut lies elsewhere (flat or tied rows) take more
+//      passes: a histogram of the row's mass and the entries of one of its
+//      bins, or a radix descent over the row's 32-bit order keys, 11, 11 and 10
+//      bits per level;
 //   4. lse = max / T + log(kept mass).
-// In either descent over a long row the second level also gathers the keys
+// A pass over 128,256 entries by one workgroup is bound by its instructions (64
+// lanes a cycle), so a pass does little per entry: float64 sums per thread
+// instead of fixed-point ones, no vote across the wave.  224 rows of 128,256,
+// top-p 0.9 in a step: 106 us with three passes of LDS atomics, 40-48 with one.
+// In the radix descent over a long row the second level also gathers the keys
 // inside the first level's bucket into LDS; when they fit, the third level
 // reads those instead of the row (the same entries, so the same integer
 // sums).
-// Masses are exp((logit - max) / T) in float32, scaled by 2^S and truncated to
-// 64-bit integers (S = 62 - ceil(log2 V), so a whole row cannot overflow);
-// integer sums make every histogram and total independent of the order of
-// the atomic adds, so the cut is deterministic.
+// Masses are exp((logit - max) / T) in float32; where atomics add them they are
+// scaled by 2^S and truncated to 64-bit integers (S = 62 - ceil(log2 V), so a
+// whole row cannot overflow), which makes every histogram and total
+// independent of the order of the adds; a row's whole mass is summed in
+// float64 in a fixed order.  The cut is deterministic either way.
 #include <hip/hip_ext.h>
 
 #include <cmath>
+#include <type_traits>
 
 #include "common.h"
 #include "launch.h"
@@ -40,21 +51,41 @@ namespace {
 constexpr int kWarpThreads = 1024;
 constexpr int kWarpWaves = kWarpThreads / kWave;
 constexpr int kBuckets = 2048;
-static_assert(kBuckets == 2 * kWarpThreads, "the level-0 total reads two buckets per thread");
 constexpr int kCand = 2048;  // candidates the small-k path can hold
 // Keys of the entries inside the first level's bucket that a descent's
 // second level gathers into LDS, so that its third level histograms them
 // instead of passing over the row again (when they fit).
 constexpr int kKeep = 16384;
 constexpr int kKeepMinV = 65536;
+// Largest entries that each thread keeps in LDS (the same space).
+constexpr int kKeepEach = 24;
+static_assert(kKeepEach * kWarpThreads >= kKeep, "one array serves both");
 
 __device__ __forceinline__ float key_value(uint32_t k) {
   return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
 }
 
-__device__ __forceinline__ unsigned long long fixed_mass(float x, float m, float inv_t, double scale) {
-  const float w = expf((x - m) * inv_t);
-  return (unsigned long long)((double)w * scale);
+// exp(t) for t <= 0, to about an ulp: 2^(t log2 e) on the hardware exponential,
+// with the product's rounding error (and log2 e's) put back to first order.
+// Half the instructions of expf, whose range checks t <= 0 does not need; the
+// pass over a row is bound by them.
+__device__ __forceinline__ float exp_neg(float t) {
+  const float h = t * kLog2e;
+  const float l = fmaf(t, 1.925963033500e-8f, fmaf(t, kLog2e, -h));  // log2 e = kLog2e + 1.92596e-8
+  const float e = __builtin_amdgcn_exp2f(h);
+  return fmaf(e, l * 0.693147180559945f, e);
+}
+
+// trunc(exp((x - m) / T) * 2^S) for x <= m, from the float32 value's bits (the
+// value is about 1 at most and S at most 62, so the shifts cover every case;
+// values below 2^-126 truncate to 0).
+__device__ __forceinline__ unsigned long long fixed_mass(float x, float m, float inv_t, int S) {
+  const uint32_t b = __float_as_uint(exp_neg((x - m) * inv_t));
+  const int sh = (int)(b >> 23) - 150 + S;
+  const uint32_t mant = (b & 0x7fffffu) | 0x800000u;
+  const unsigned long long up = (unsigned long long)mant << max(sh, 0);
+  const uint32_t down = sh > -24 ? mant >> (max(-sh, 0) & 31) : 0u;
+  return (b >> 23) == 0 ? 0ull : (sh >= 0 ? up : (unsigned long long)down);
 }
 
 __device__ __forceinline__ unsigned long long shfl_xor_u64(unsigned long long v, int mask) {
@@ -214,16 +245,18 @@ __device__ void select_bucket(const uint32_t* hcnt, const unsigned long long* hm
 
 __global__ __launch_bounds__(kWarpThreads)
 void warp_kernel(int V, const float* __restrict__ logits, float inv_t, int greedy, int top_k, float top_p,
-                 double scale, WarpRow* __restrict__ out, float* __restrict__ row_lse,
+                 int scale, const float2* __restrict__ partials, int ntiles, int tile_n, WarpRow* __restrict__ out, float* __restrict__ row_lse,
                  float* __restrict__ row_min_logit) {
   __shared__ uint32_t hcnt[kBuckets];
   __shared__ unsigned long long hmass[kBuckets];
   __shared__ uint32_t w_key[kWarpWaves];
   __shared__ int w_idx[kWarpWaves];
+  __shared__ uint32_t w_low[kWarpWaves], s_low;
   __shared__ unsigned long long w_sum[kWarpWaves];
+  __shared__ double w_mass[kWarpWaves];
   __shared__ uint32_t s_kmax, s_bucket, s_cnt_above;
   __shared__ int s_amax;
-  __shared__ unsigned long long s_mass_above, s_total;
+  __shared__ unsigned long long s_mass_above;
   __shared__ unsigned long long s_list[kWarpWaves][kWave];
   __shared__ unsigned long long s_cand[kCand];
   __shared__ uint32_t s_n, s_bound, s_theta, s_pdone;
@@ -233,13 +266,13 @@ void warp_kernel(int V, const float* __restrict__ logits, float inv_t, int greed
   const int row = blockIdx.x;
   const float* x = logits + (int64_t)row * V;
   float m_row = 0.f;  // the row's largest logit, once known
-  __shared__ uint32_t s_keep[kKeep];
+  __shared__ uint32_t s_keep[kKeepEach * kWarpThreads];
   __shared__ uint32_t s_nkeep;
 
-  // One level of a radix descent: histogram (counts and masses) of the
-  // entries whose key is at least `floor` and whose bits above the level's
-  // digit equal `prefix`.  Level 1 also gathers those entries' keys; level 2
-  // reads the gathered keys when all of them fit.
+  // One level of a radix descent over the row: histogram (counts and masses)
+  // of the entries whose key is at least `floor` and whose bits above the
+  // level's digit equal `prefix`.  Level 1 also gathers those entries' keys;
+  // level 2 reads the gathered keys when all of them fit.
   auto histogram = [&](int level, const Level& lv, uint32_t prefix, uint32_t floor) {
     for (int i = threadIdx.x; i < lv.nb; i += kWarpThreads) {
       hcnt[i] = 0;
@@ -288,22 +321,82 @@ void warp_kernel(int V, const float* __restrict__ logits, float inv_t, int greed
       i = oi;
     }
   };
+  // With the projection's tile statistics, from the tile maxima: only greedy
+  // needs the entry itself, and then reads the tiles that reach the maximum.
+  const float2* tiles = partials != nullptr ? partials + (int64_t)row * ntiles : nullptr;
+  // f(v, x[v]) for every entry of the tiles whose maximum reaches `bound`
+  // (tiles w, w + 16, ... on wave w).
+  auto tile_pass = [&](float bound, auto&& f) {
+    for (int base = 0; base < ntiles; base += kWarpThreads) {
+      const int t = base + lane * kWarpWaves + wave;
+      const float tm = tiles[min(t, ntiles - 1)].x;
+      unsigned long long todo = __ballot(t < ntiles && tm >= bound);
+      while (todo) {
+        const int v0 = (base + (__ffsll(todo) - 1) * kWarpWaves + wave) * tile_n;
+        todo &= todo - 1;
+        const int v1 = min(V, v0 + tile_n);
+        for (int vb = v0; vb < v1; vb += 8 * kWave) {
+          float r[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) r[e] = x[min(vb + e * kWave + lane, v1 - 1)];
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            if (vb + e * kWave + lane < v1) f(vb + e * kWave + lane, r[e]);
+        }
+      }
+    }
+  };
+  const bool by_tiles = tiles != nullptr && (greedy || top_k == 0 || top_k >= V || top_k > kWave || top_k <= ntiles);
   uint32_t bk = 0;
   int bi = 0x7fffffff;
-  row_pass(x, V, [&](int v, float xv) { merge(bk, bi, order_key(xv), v); });
-  const unsigned long long tkey = bi == 0x7fffffff ? 0ull : entry_key(bk, bi);  // this thread's best entry
-  for (int off = 32; off >= 1; off >>= 1) merge(bk, bi, __shfl_xor(bk, off), __shfl_xor(bi, off));
+  if (by_tiles) {
+    for (int t = tid; t < ntiles; t += kWarpThreads) merge(bk, bi, order_key(tiles[t].x), t);
+  } else {
+    row_pass(x, V, [&](int v, float xv) { merge(bk, bi, order_key(xv), v); });
+  }
+  // This thread's best entry (or tile): a lower bound of one entry of the row.
+  const unsigned long long tkey = bi == 0x7fffffff ? 0ull : entry_key(bk, bi);
+  // The threads' smallest, without the thread that holds a partial last tile.
+  const bool part = by_tiles && ntiles > 1 && V % tile_n != 0 && tid == (ntiles - 1) % kWarpThreads;
+  uint32_t low = bi == 0x7fffffff || part ? 0xffffffffu : bk;
+  for (int off = 32; off >= 1; off >>= 1) {
+    merge(bk, bi, __shfl_xor(bk, off), __shfl_xor(bi, off));
+    low = min(low, (uint32_t)__shfl_xor((int)low, off));
+  }
+  if (greedy && by_tiles) {
+    __shared__ float s_top;
+    if (lane == 0) w_key[wave] = bk;
+    __syncthreads();
+    if (tid == 0) {
+      uint32_t k = w_key[0];
+      for (int w = 1; w < kWarpWaves; ++w) k = max(k, w_key[w]);
+      s_top = key_value(k);
+    }
+    __syncthreads();
+    const float top = s_top;
+    bk = 0;
+    bi = 0x7fffffff;
+    tile_pass(top, [&](int v, float xv) { merge(bk, bi, order_key(xv), v); });
+    for (int off = 32; off >= 1; off >>= 1) merge(bk, bi, __shfl_xor(bk, off), __shfl_xor(bi, off));
+    __syncthreads();
+  }
   if (lane == 0) {
     w_key[wave] = bk;
     w_idx[wave] = bi;
+    w_low[wave] = low;
   }
   __syncthreads();
   if (tid == 0) {
     uint32_t k = w_key[0];
     int i = w_idx[0];
-    for (int w = 1; w < kWarpWaves; ++w) merge(k, i, w_key[w], w_idx[w]);
+    uint32_t lo = w_low[0];
+    for (int w = 1; w < kWarpWaves; ++w) {
+      merge(k, i, w_key[w], w_idx[w]);
+      lo = min(lo, w_low[w]);
+    }
     s_kmax = k;
     s_amax = i;
+    s_low = lo;
   }
   __syncthreads();
   const int amax = s_amax;
@@ -322,7 +415,6 @@ void warp_kernel(int V, const float* __restrict__ logits, float inv_t, int greed
   uint32_t theta = 0;
   unsigned long long W = 0;
   bool have_k = false, have_p = false;
-  bool w_known = true;  // W holds the kept mass (false: the first top-p level supplies it)
   if (top_k >= 1 && top_k <= kWave && top_k < V) {
     // Small k: the k-th largest of the threads' best entries bounds the k-th
     // largest logit from below (k threads reach it), so the entries at or
@@ -340,14 +432,16 @@ void warp_kernel(int V, const float* __restrict__ logits, float inv_t, int greed
       }
     }
     __syncthreads();
-    const uint32_t bound = s_bound;
-    row_pass(x, V, [&](int v, float xv) {
-      const uint32_t k = order_key(xv);
-      if (k >= bound) {
+    // As values (-0 equal to +0: a tile maximum may be either); a superset.
+    const float bound = key_value(s_bound);
+    auto take = [&](int v, float xv) {
+      if (xv >= bound) {
         const uint32_t i = atomicAdd(&s_n, 1u);
-        if (i < (uint32_t)kCand) s_cand[i] = entry_key(k, v);
+        if (i < (uint32_t)kCand) s_cand[i] = entry_key(order_key(xv), v);
       }
-    });
+    };
+    if (by_tiles) tile_pass(bound, take);
+    else row_pass(x, V, take);
     __syncthreads();
     const uint32_t n = s_n;
     if (n <= (uint32_t)kCand) {  // otherwise (masses of ties at the bound) the radix descent below
@@ -403,8 +497,145 @@ void warp_kernel(int V, const float* __restrict__ logits, float inv_t, int greed
       have_p = s_pdone != 0;
     }
   }
+  // Other cuts: the largest entries (value at least `bound`, a few thousand)
+  // are kept in LDS, each thread its own, and the cut is found among them when
+  // they hold it: top_k of them, or top_p of the row's mass (summed in the same
+  // pass, per thread in float64).  The bound is the smallest tile maximum where
+  // that leaves top_k entries, else 0.15 of the tile maxima's spread below it
+  // (3 to 10 % of a normal row), or without tiles a tenth of the spread above the
+  // smallest of the threads' maxima (3 % of a 128,256-entry normal row); a
+  // bound that keeps too many or too few only costs time, the cut is then
+  // found from the whole row.
+  const bool cut_k = top_k >= 1 && top_k < V;
+  bool among = false;  // the cut is among the kept entries
+  int mine = 0;        // this thread's, at s_keep[i * kWarpThreads + tid]
+  uint32_t kbase = 0;  // a key no kept entry is below
+  uint32_t kmax = m == 0.f ? order_key(0.f) : s_kmax;  // and one none is above
+  double mass = 0.0;   // of the row, this thread's share
+  const bool whole = !have_k && !cut_k;
+  if (!have_k && (cut_k || top_p < 1.f)) {
+    const float lowest = key_value(s_low);
+    const float bound = !by_tiles ? lowest + 0.1f * (m - lowest)
+                                  : (cut_k && top_k <= ntiles ? lowest : lowest - 0.15f * (m - lowest));
+    kbase = order_key(bound == 0.f ? -0.f : bound);  // -0 passes as +0 does
+    for (int i = tid; i < kBuckets; i += kWarpThreads) hmass[i] = 0;
+    auto take = [&](int, float xv) {
+      if (xv >= bound) {
+        if (mine < kKeepEach) s_keep[mine * kWarpThreads + tid] = __float_as_uint(xv);
+        ++mine;
+      }
+    };
+    if (!cut_k)
+      row_pass(x, V, [&](int v, float xv) {
+        mass += (double)exp_neg((xv - m) * inv_t);
+        take(v, xv);
+      });
+    else if (by_tiles)
+      tile_pass(bound, take);
+    else
+      row_pass(x, V, take);
+    // Kept values to keys; their count, or their mass.
+    unsigned long long near = cut_k ? (unsigned long long)mine : 0ull;
+    for (int i = 0; i < min(mine, kKeepEach); ++i) {
+      const float xv = __uint_as_float(s_keep[i * kWarpThreads + tid]);
+      s_keep[i * kWarpThreads + tid] = order_key(xv);
+      if (!cut_k) near += fixed_mass(xv, m, inv_t, scale);
+    }
+    const bool over = __ballot(mine > kKeepEach) != 0;
+    for (int off = 32; off >= 1; off >>= 1) near += shfl_xor_u64(near, off);
+    if (lane == 0) {
+      w_sum[wave] = near;
+      w_key[wave] = over;
+    }
+  } else if (whole) {
+    row_pass(x, V, [&](int, float xv) { mass += (double)exp_neg((xv - m) * inv_t); });
+  }
+  if (whole) {
+    mass = wave_sum_f64(mass);
+    if (lane == 0) w_mass[wave] = mass;
+  }
+  __syncthreads();
+  if (whole) {
+    double all = 0.0;
+    for (int w = 0; w < kWarpWaves; ++w) all += w_mass[w];
+    W = (unsigned long long)ldexp(all, scale);
+  }
+  if (!have_k && (cut_k || top_p < 1.f)) {
+    unsigned long long near = 0;
+    uint32_t over = 0;
+    for (int w = 0; w < kWarpWaves; ++w) {
+      near += w_sum[w];
+      over |= w_key[w];
+    }
+    const unsigned long long target =
+        cut_k ? (unsigned long long)top_k : max((unsigned long long)ceil((double)top_p * (double)W), 1ull);
+    among = over == 0 && near >= target;
+    __syncthreads();
+  }
+  // Radix descent over the kept entries, on their distance from kbase, in
+  // digits of eight bits from the highest bit in use (whole keys share their
+  // top bits: few buckets, and atomics that collide): the first key from the
+  // top at which the running count (or mass) of the entries at or above
+  // `floor` reaches `need`.  A level takes the next of hmass's eight cleared
+  // histograms of 256 and one barrier; every wave selects its bucket for
+  // itself.  *upto: the count (or mass) down to that key.
+  auto near_cut = [&](auto by_mass, int hist0, unsigned long long need, uint32_t floor, unsigned long long* upto) {
+    constexpr int kBits = 8, kBins = 1 << kBits;
+    int shift = 32 - __clz((int)((kmax - kbase) | 1u));
+    uint32_t prefix = 0;
+    unsigned long long above = 0;
+    for (int level = hist0; shift > 0; ++level) {
+      const int top_shift = shift;
+      const int width = min(shift, kBits);
+      shift -= width;
+      unsigned long long* h = hmass + level * kBins;
+      for (int i = 0; i < mine; ++i) {
+        const uint32_t k = s_keep[i * kWarpThreads + tid];
+        const uint32_t d = k - kbase;
+        if (k >= floor && (top_shift >= 32 || (d >> top_shift) == prefix))
+          atomicAdd(&h[(d >> shift) & ((1u << width) - 1)],
+                    decltype(by_mass)::value ? fixed_mass(key_value(k), m, inv_t, scale) : 1ull);
+      }
+      __syncthreads();
+      // Lane l: buckets 255 - 4l .. 252 - 4l, from the top.
+      uint64_t c[4], own = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        c[i] = h[kBins - 1 - 4 * lane - i];
+        own += c[i];
+      }
+      const uint64_t inc = wave_inclusive_scan_u64(own);
+      const unsigned long long hit = __ballot(above + inc >= need);
+      const int at = hit ? __ffsll(hit) - 1 : kWave - 1;
+      uint64_t run = above + inc - own;  // of the buckets above this lane's
+      int b = kBins - 1 - 4 * lane;
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        const bool on = run + c[i] < need && b == kBins - 1 - 4 * lane - i;
+        run += on ? c[i] : 0ull;
+        b -= on ? 1 : 0;
+      }
+      above = lane_u64(run, at);
+      b = __builtin_amdgcn_readlane(b, at);
+      prefix = (prefix << width) | (uint32_t)b;
+      *upto = above + h[b];
+    }
+    return kbase + prefix;
+  };
   if (have_k) {
-  } else if (top_k >= 1 && top_k < V) {
+  } else if (cut_k && among) {
+    unsigned long long kept;
+    theta = near_cut(std::false_type{}, 0, (unsigned long long)top_k, 0u, &kept);
+    unsigned long long sum = 0;
+    for (int i = 0; i < mine; ++i) {
+      const uint32_t k = s_keep[i * kWarpThreads + tid];
+      if (k >= theta) sum += fixed_mass(key_value(k), m, inv_t, scale);
+    }
+    for (int off = 32; off >= 1; off >>= 1) sum += shfl_xor_u64(sum, off);
+    if (lane == 0) w_sum[wave] = sum;
+    __syncthreads();
+    for (int w = 0; w < kWarpWaves; ++w) W += w_sum[w];
+  } else if (cut_k) {
     uint32_t prefix = 0, krem = (uint32_t)top_k;
     unsigned long long above = 0;
     for (int level = 0; level < 3; ++level) {
@@ -420,52 +651,80 @@ void warp_kernel(int V, const float* __restrict__ logits, float inv_t, int greed
       __syncthreads();
     }
     theta = prefix;
-  } else if (top_p < 1.f) {
-    // No top-k cut: the first level of the top-p descent histograms every
-    // entry, and W is the total of that histogram (no pass of its own).
-    w_known = false;
-  } else {
-    unsigned long long sum = 0;
-    row_pass(x, V, [&](int, float xv) { sum += fixed_mass(xv, m, inv_t, scale); });
-    for (int off = 32; off >= 1; off >>= 1) sum += shfl_xor_u64(sum, off);
-    if (lane == 0) w_sum[wave] = sum;
-    __syncthreads();
-    if (tid == 0) {
-      unsigned long long t = 0;
-      for (int w = 0; w < kWarpWaves; ++w) t += w_sum[w];
-      s_total = t;
-    }
-    __syncthreads();
-    W = s_total;
   }
 
   if (top_p < 1.f && !have_p) {
-    unsigned long long target = 0;
-    auto set_target = [&]() {
-      target = (unsigned long long)ceil((double)top_p * (double)W);
-      target = target < 1 ? 1 : (target > W ? W : target);
-    };
-    if (w_known) set_target();
+    unsigned long long target = (unsigned long long)ceil((double)top_p * (double)W);
+    target = target < 1 ? 1 : (target > W ? W : target);
     uint32_t prefix = 0;
     unsigned long long above = 0;
-    for (int level = 0; level < 3; ++level) {
+    if (!among && whole) {
+      // The cut lies below the kept entries (a flat row), or too many were
+      // kept: one pass histograms the row's mass over 2048 bins of 1/64 nat from
+      // the maximum, another keeps the entries of the bin where the running
+      // mass reaches the target.
+      auto bin_of = [&](float xv) { return (int)min((m - xv) * inv_t * 64.f, (float)(kBuckets - 1)); };
+      for (int i = tid; i < kBuckets; i += kWarpThreads) {
+        hmass[i] = 0;
+        hcnt[i] = 0;
+      }
+      __syncthreads();
+      row_pass(x, V, [&](int, float xv) {
+        const unsigned long long w = fixed_mass(xv, m, inv_t, scale);
+        if (w != 0) atomicAdd(&hmass[kBuckets - 1 - bin_of(xv)], w);  // far entries would meet in one bin
+      });
+      __syncthreads();
+      if (wave == 0) select_bucket<true>(hcnt, hmass, kBuckets, target, &s_bucket, &s_cnt_above, &s_mass_above);
+      __syncthreads();
+      const int bin = kBuckets - 1 - (int)s_bucket;
+      const unsigned long long bin_above = s_mass_above;
+      for (int i = tid; i < kBuckets; i += kWarpThreads) hmass[i] = 0;
+      mine = 0;
+      uint32_t lo = 0xffffffffu, hi = 0;
+      row_pass(x, V, [&](int, float xv) {
+        if (bin_of(xv) == bin) {
+          const uint32_t k = order_key(xv);
+          lo = min(lo, k);
+          hi = max(hi, k);
+          if (mine < kKeepEach) s_keep[mine * kWarpThreads + tid] = k;
+          ++mine;
+        }
+      });
+      const bool over = __ballot(mine > kKeepEach) != 0;
+      for (int off = 32; off >= 1; off >>= 1) {
+        lo = min(lo, (uint32_t)__shfl_xor((int)lo, off));
+        hi = max(hi, (uint32_t)__shfl_xor((int)hi, off));
+      }
+      if (lane == 0) {
+        w_key[wave] = hi;
+        w_low[wave] = lo;
+        w_idx[wave] = over;
+      }
+      __syncthreads();
+      kbase = 0xffffffffu;
+      kmax = 0;
+      int full = 0;
+      for (int w = 0; w < kWarpWaves; ++w) {
+        kbase = min(kbase, w_low[w]);
+        kmax = max(kmax, w_key[w]);
+        full |= w_idx[w];
+      }
+      // Masses summed in 64-bit integers here and in float64 in W may put the
+      // target a rounding past the last bin: the radix descent handles that too.
+      if (full == 0 && kbase <= kmax && target > bin_above) {
+        among = true;
+        above = bin_above;
+      }
+      __syncthreads();
+    }
+    if (among) {
+      prefix = near_cut(std::true_type{}, kBuckets / 512, target - above, theta, &W);
+      W += above;
+      above = 0;
+    }
+    for (int level = 0; level < 3 && !among; ++level) {
       const Level lv = level_of(level);
       histogram(level, lv, prefix, theta);
-      if (!w_known) {  // level 0 over every entry: W = the histogram's total
-        unsigned long long t = hmass[tid] + hmass[tid + kWarpThreads];
-        for (int off = 32; off >= 1; off >>= 1) t += shfl_xor_u64(t, off);
-        if (lane == 0) w_sum[wave] = t;
-        __syncthreads();
-        if (tid == 0) {
-          unsigned long long tt = 0;
-          for (int w = 0; w < kWarpWaves; ++w) tt += w_sum[w];
-          s_total = tt;
-        }
-        __syncthreads();
-        W = s_total;
-        w_known = true;
-        set_target();
-      }
       if (wave == 0)
         select_bucket<true>(hcnt, hmass, lv.nb, target - above, &s_bucket, &s_cnt_above, &s_mass_above);
       __syncthreads();
@@ -479,7 +738,7 @@ void warp_kernel(int V, const float* __restrict__ logits, float inv_t, int greed
   }
 
   if (tid == 0) {
-    const float lse = (float)((double)m * (double)inv_t + log((double)W / scale));
+    const float lse = (float)((double)m * (double)inv_t + log(ldexp((double)W, -scale)));
     out[row] = WarpRow{inv_t, theta, lse, -1};
     row_lse[row] = lse;
     row_min_logit[row] = theta == 0 ? -INFINITY : key_value(theta);
@@ -489,15 +748,16 @@ void warp_kernel(int V, const float* __restrict__ logits, float inv_t, int greed
 }  // namespace
 
 hipError_t launch_warp(int M, int V, const float* logits, float temperature, int top_k, float top_p, WarpRow* out,
-                       float* row_lse, float* row_min_logit, hipStream_t stream, hipEvent_t ev_start) {
+                       float* row_lse, float* row_min_logit, hipStream_t stream, hipEvent_t ev_start, const float2* partials,
+                       int ntiles, int tile_n) {
   if (M <= 0) return hipSuccess;
   const int greedy = temperature == 0.f;
   const float inv_t = greedy ? 0.f : 1.f / temperature;  // float32 division, correctly rounded
   int bits = 0;
   while ((int64_t(1) << bits) < V) ++bits;
-  const double scale = std::ldexp(1.0, 62 - bits);
+  const int scale = 62 - bits;
   hipExtLaunchKernelGGL(warp_kernel, dim3(M), dim3(kWarpThreads), 0, stream, ev_start, nullptr, 0, V, logits, inv_t,
-                        greedy, top_k, top_p, scale, out, row_lse, row_min_logit);
+                        greedy, top_k, top_p, scale, partials, ntiles, tile_n, out, row_lse, row_min_logit);
   return hipGetLastError();
 }
 

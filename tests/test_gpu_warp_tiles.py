@@ -1,0 +1,71 @@
+"""The warp inside a sampled step starts from the projection's tile maxima and
+looks for the cut among gathered entries; the standalone call starts from the
+row.  On the step's own logits both must give the same bits (the sums are
+integers over the same entries): greedy, top-k below, at and above 64 and above
+the number of tiles, top-p over peaked, flat and tied rows (the gathered set
+then misses the mass or overflows and the whole row is searched), one tile and
+several, both weight layouts.  A peaked and a flat row are also checked against
+the oracle's cut."""
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2601_21622_amd as sd
+
+from gpu_util import announce, to_np
+from test_gpu_sampling import _check_cut
+
+pytestmark = pytest.mark.gpu
+
+SETTINGS = [(0.0, 0, 1.0), (0.7, 0, 1.0), (1.0, 0, 0.9), (1.0, 0, 0.9999), (0.8, 40, 0.9), (1.0, 64, 1.0), (1.0, 65, 0.5),
+            (0.6, 200, 0.95), (1.0, 900, 0.9), (1.3, 1, 1.0)]
+# rows (B, G), K, V, scale of the logits (0: all equal), ties (distinct weight rows; 0: all distinct)
+SHAPES = {
+    "peaked_128k": ((2, 3), 64, 128256, 8.0, 0), "flat_100k": ((2, 2), 64, 100003, 0.3, 0),
+    "tied_70k": ((1, 2), 64, 70001, 2.0, 7), "equal_33k": ((1, 2), 32, 33000, 0.0, 0),
+    "one_tile": ((2, 2), 32, 31, 2.0, 0), "deep_5k": ((14, 5), 64, 5001, 3.0, 0),
+}
+
+
+@pytest.mark.parametrize("T,k,p", SETTINGS)
+@pytest.mark.parametrize("shape", sorted(SHAPES))
+def test_step_warp_equals_standalone(shape, T, k, p):
+    (B, G), K, V, scale, ties = SHAPES[shape]
+    M, D, L = B * G, 64, 8
+    announce(f"warp tiles shape={shape} T={T} k={k} p={p}")
+    g = torch.Generator().manual_seed(V + k)
+    h = torch.randn(M, K, generator=g).bfloat16().cuda()
+    w = torch.randn(ties or V, K, generator=g) * (scale / K ** 0.5)
+    if ties:
+        w = w[torch.randint(0, ties, (V,), generator=g)]
+    w = w.bfloat16().cuda()
+    dims = sd.Dims(B, G - 1, 1, 1, D, K, V, sd.SD_DTYPE_BF16, 0)
+    if k % 2 == 0:
+        dims = dims.with_flags(sd.SD_FLAG_PACKED_VOCAB)
+        wp = torch.empty(sd.sd_vocab_packed_bytes(dims) // 2, dtype=torch.bfloat16, device="cuda")
+        sd.sd_pack_vocab(dims, w, wp)
+        w = wp
+    kv_len, kv_off = np.full(B, L, np.int32), np.arange(B, dtype=np.int64) * L * D
+    kv = torch.randn(B * L * D, generator=g).bfloat16().cuda()
+    q = torch.randn(B, G, 1, D, generator=g).bfloat16().cuda()
+    qd = torch.softmax(torch.randn(B, G - 1, V, generator=g), 2).cuda()
+    draft = torch.randint(0, V, (B, G - 1), generator=g).int().cuda()
+    u = torch.rand(B, G, generator=g).cuda()
+    need = sd.sd_workspace_bytes(dims, L)
+
+    def outs():
+        f = lambda *s, dt=torch.float32: torch.full(s, -7, dtype=dt, device="cuda")  # noqa: E731
+        return f(M), f(M), f(B, dt=torch.int32), f(B, G, dt=torch.int32), f(B, dt=torch.int32)
+
+    attn, logits = torch.empty_like(q), torch.empty(M, V, device="cuda")
+    got, want = outs(), outs()
+    sampling = sd.Sampling(T, k, p)
+    sd.sd_verify_step_sampled(dims, sampling, q, kv, kv, kv_off, kv_len, 0.125, h, w, qd, draft, u, attn, logits, *got,
+                              torch.full((need,), 0x5A, dtype=torch.uint8, device="cuda"))
+    sd.sd_accept_resample_sampled(dims, sampling, logits, qd, draft, u, kv_len, *want,
+                                  torch.full((need,), 0xA5, dtype=torch.uint8, device="cuda"))
+    for a, b in zip(got, want):
+        assert np.array_equal(to_np(a), to_np(b))
+    if scale >= 0.3 and not ties:
+        _check_cut(to_np(logits)[:2], T, k, p, to_np(got[0])[:2], to_np(got[1])[:2])
