@@ -84,7 +84,8 @@ size_t attention_ws(const sd_dims_t* d, int64_t chunks) {
   return align_up(attn_partial_bytes(chunks, s.Hkv, s.rows, s.D));
 }
 
-// Tree verification: the ancestor masks, at the start of the workspace.
+// Tree verification: reserved at the start of the workspace (8 bytes per
+// position; the kernels derive the ancestor masks themselves).
 size_t tree_ws(const sd_dims_t* d) { return align_up(sizeof(uint64_t) * static_cast<size_t>(d->batch) * (d->gamma + 1)); }
 
 size_t logits_ws(const sd_dims_t* d) {
@@ -131,11 +132,13 @@ int hip_status(hipError_t e) { return e == hipSuccess ? SD_OK : SD_ERR_HIP; }
 // Enqueue attention (partials + combine) for all requests, in launches of at
 // most kMaxReqPerLaunch requests whose tables ride in the kernel arguments.
 // With `deferred`, the merges are not launched: one CombineJob per launch is
-// appended there instead, for a later launch to carry.
+// appended there instead, for a later launch to carry.  With `pack`, the last
+// launch carries that repacking of the projection's hidden rows.
 int run_attention(const sd_dims_t* d, const void* q, const void* k, const void* v, const int64_t* kv_off,
                   const int32_t* kv_len, float scale, void* out, void* ws, hipStream_t stream,
-                  hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr, const uint64_t* anc = nullptr,
-                  const sd_kv_pages_t* pages = nullptr, std::vector<CombineJob>* deferred = nullptr) {
+                  hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr, const int32_t* parent = nullptr,
+                  const sd_kv_pages_t* pages = nullptr, std::vector<CombineJob>* deferred = nullptr,
+                  const PackJob* pack = nullptr) {
   const AttnShape s = attn_shape(d, scale, kv_len, pages != nullptr ? pages->page_size : 0);
   const int64_t chunks = total_chunks(kv_len, d->batch, s.chunk_keys);
   const AttnPartials parts = attn_carve(ws, chunks, s.Hkv, s.rows, s.D);
@@ -146,7 +149,7 @@ int run_attention(const sd_dims_t* d, const void* q, const void* k, const void* 
     bt.nreq = std::min(kMaxReqPerLaunch, d->batch - r0);
     bt.req0 = r0;
     bt.chunk_base = static_cast<int32_t>(chunk_base);
-    bt.anc = anc;
+    bt.parent = parent;
     if (pages != nullptr) {
       bt.pages = pages->block_table;
       bt.page_shift = log2_exact(pages->page_size);
@@ -163,7 +166,7 @@ int run_attention(const sd_dims_t* d, const void* q, const void* k, const void* 
     bt.chunk_prefix[bt.nreq] = acc;
     const bool first = r0 == 0, last = r0 + kMaxReqPerLaunch >= d->batch;
     hipError_t e = launch_attention(d->dtype, s, bt, acc, q, k, v, parts, stream, first ? ev_start : nullptr,
-                                    last ? ev_stop : nullptr);
+                                    last ? ev_stop : nullptr, last ? pack : nullptr);
     if (e != hipSuccess) return SD_ERR_HIP;
     if (deferred != nullptr) {
       CombineJob cj;
@@ -364,11 +367,9 @@ int sd_verify_attention_tree(const sd_dims_t* dims, const void* q, const void* k
   const AttnShape s = attn_shape(dims, scale, kv_len);
   if (workspace_bytes < tree_ws(dims) + attention_ws(dims, total_chunks(kv_len, dims->batch, s.chunk_keys)))
     return SD_ERR_WORKSPACE;
-  hipStream_t stm = static_cast<hipStream_t>(stream);
-  uint64_t* masks = static_cast<uint64_t*>(workspace);
-  if (launch_tree_masks(dims->batch, dims->gamma, parent, masks, stm) != hipSuccess) return SD_ERR_HIP;
   return run_attention(dims, q, k_pool, v_pool, kv_off, kv_len, scale, out,
-                       static_cast<char*>(workspace) + tree_ws(dims), stm, nullptr, nullptr, masks);
+                       static_cast<char*>(workspace) + tree_ws(dims), static_cast<hipStream_t>(stream), nullptr,
+                       nullptr, parent);
 }
 
 int sd_verify_logits(const sd_dims_t* dims, const void* hidden, const void* w_vocab, float* logits,
@@ -476,21 +477,24 @@ int verify_step(const sd_dims_t* dims, const void* q, const void* k_pool, const 
   if (kernel_events != nullptr)
     for (int i = 0; i < 6; ++i) ev[i] = static_cast<hipEvent_t>(kernel_events[i]);
   hipStream_t stm = static_cast<hipStream_t>(stream);
-  std::vector<CombineJob> merges;
-  st = run_attention(dims, q, k_pool, v_pool, kv_off, kv_len, scale, attn_out, workspace, stm, ev[0], ev[1],
-                     nullptr, pages, defer ? &merges : nullptr);
-  if (st != SD_OK) return st;
   // The vocabulary statistics come first in their region and the acceptance
   // sums after them, since the fold reads the former while the segment kernel
   // writes the latter.
   void* vws = static_cast<char*>(workspace) + base;
   const VocabPlan vp = vocab_plan(dims->dtype, dims->batch * (dims->gamma + 1), dims->hidden, dims->vocab, (dims->flags & SD_FLAG_PACKED_VOCAB) != 0);
   float2* partials = static_cast<float2*>(vws);
-  // The projection launch clears the acceptance's arrival counters, so the
-  // acceptance runs as one launch.
+  // The projection's launches (or the repacking that the attention launch
+  // carries) clear the acceptance's arrival counters, so the acceptance runs
+  // as one launch.
   void* acc_ws = static_cast<char*>(vws) + logits_ws(dims);
+  int* arrivals = accept_arrivals(acc_ws, dims->batch, dims->vocab);
+  const PackJob pack = defer ? vocab_pack_job(vp, hidden, vws, arrivals, dims->batch) : PackJob{};
+  std::vector<CombineJob> merges;
+  st = run_attention(dims, q, k_pool, v_pool, kv_off, kv_len, scale, attn_out, workspace, stm, ev[0], ev[1],
+                     nullptr, pages, defer ? &merges : nullptr, &pack);
+  if (st != SD_OK) return st;
   if (launch_vocab(dims->dtype, vp, hidden != nullptr ? hidden : attn_out, w_vocab, logits, vws, stm, ev[2], ev[3],
-                   accept_arrivals(acc_ws, dims->batch, dims->vocab), dims->batch) != hipSuccess)
+                   arrivals, dims->batch, pack.nblocks > 0) != hipSuccess)
     return SD_ERR_HIP;
   return run_accept(dims, logits, row_lse, partials, vp.ntiles, q_draft, draft_tok, u, kv_len, accept_len, out_tok,
                     new_kv_len, acc_ws, stm, ev[4], ev[5], nullptr, defer ? &merges : nullptr, true);
@@ -559,18 +563,18 @@ int sd_verify_step_sampled(const sd_dims_t* dims, const sd_sampling_t* sampling,
   if (kernel_events != nullptr)
     for (int i = 0; i < 6; ++i) ev[i] = static_cast<hipEvent_t>(kernel_events[i]);
   hipStream_t stm = static_cast<hipStream_t>(stream);
-  std::vector<CombineJob> merges;
-  st = run_attention(dims, q, k_pool, v_pool, kv_off, kv_len, scale, attn_out, workspace, stm, ev[0], ev[1], nullptr,
-                     nullptr, defer ? &merges : nullptr);
-  if (st != SD_OK) return st;
   const VocabPlan vp = vocab_plan(dims->dtype, dims->batch * (dims->gamma + 1), dims->hidden, dims->vocab,
                                   (dims->flags & SD_FLAG_PACKED_VOCAB) != 0);
-  // The projection launch clears the acceptance's arrival counters, so the
-  // acceptance runs as one launch.
   void* vws = static_cast<char*>(workspace) + (defer ? attn_bytes : 0);
   void* acc_ws = static_cast<char*>(vws) + logits_ws(dims);
+  int* arrivals = accept_arrivals(acc_ws, dims->batch, dims->vocab);
+  const PackJob pack = defer ? vocab_pack_job(vp, hidden, vws, arrivals, dims->batch) : PackJob{};
+  std::vector<CombineJob> merges;
+  st = run_attention(dims, q, k_pool, v_pool, kv_off, kv_len, scale, attn_out, workspace, stm, ev[0], ev[1], nullptr,
+                     nullptr, defer ? &merges : nullptr, &pack);
+  if (st != SD_OK) return st;
   if (launch_vocab(dims->dtype, vp, hidden != nullptr ? hidden : attn_out, w_vocab, logits, vws, stm, ev[2],
-                   ev[3], accept_arrivals(acc_ws, dims->batch, dims->vocab), dims->batch) != hipSuccess)
+                   ev[3], arrivals, dims->batch, pack.nblocks > 0) != hipSuccess)
     return SD_ERR_HIP;
   WarpRow* warp = reinterpret_cast<WarpRow*>(static_cast<char*>(acc_ws) + accept_ws(dims));
   if (launch_warp(dims->batch * (dims->gamma + 1), dims->vocab, logits, sampling->temperature, sampling->top_k,
@@ -626,8 +630,8 @@ int sd_verify_step_tree(const sd_dims_t* dims, const void* q, const void* k_pool
   const AttnShape s = attn_shape(dims, scale, kv_len);
   const size_t attn_bytes = tree_ws(dims) + attention_ws(dims, total_chunks(kv_len, dims->batch, s.chunk_keys));
   // As in the chain step: with the caller's hidden rows the attention merge
-  // rides in the acceptance's last launch, and the masks and partials keep
-  // their region: [masks][partials][projection][acceptance].
+  // rides in the acceptance's last launch, and the partials keep their region:
+  // [reserved][partials][projection][acceptance].
   const bool defer = hidden != nullptr;
   const size_t base = defer ? attn_bytes : 0;
   const size_t need = defer ? attn_bytes + logits_ws(dims) + accept_stage_ws(dims)
@@ -638,22 +642,21 @@ int sd_verify_step_tree(const sd_dims_t* dims, const void* q, const void* k_pool
   if (kernel_events != nullptr)
     for (int i = 0; i < 6; ++i) ev[i] = static_cast<hipEvent_t>(kernel_events[i]);
   hipStream_t stm = static_cast<hipStream_t>(stream);
-  uint64_t* masks = static_cast<uint64_t*>(workspace);
-  if (launch_tree_masks(dims->batch, dims->gamma, parent, masks, stm) != hipSuccess) return SD_ERR_HIP;
-  std::vector<CombineJob> merges;
-  st = run_attention(dims, q, k_pool, v_pool, kv_off, kv_len, scale, attn_out,
-                     static_cast<char*>(workspace) + tree_ws(dims), stm, ev[0], ev[1], masks, nullptr,
-                     defer ? &merges : nullptr);
-  if (st != SD_OK) return st;
   void* vws = static_cast<char*>(workspace) + base;
-  // The projection launch clears the acceptance's arrival counters; the walk
-  // launch folds the row log-sum-exps from the projection's statistics, and
-  // the final draw runs as one launch.
+  // The walk launch folds the row log-sum-exps from the projection's
+  // statistics, and the final draw runs as one launch.
   const VocabPlan vp = vocab_plan(dims->dtype, dims->batch * (dims->gamma + 1), dims->hidden, dims->vocab,
                                   (dims->flags & SD_FLAG_PACKED_VOCAB) != 0);
   void* acc_ws = static_cast<char*>(vws) + logits_ws(dims);
+  int* arrivals = accept_arrivals(acc_ws, dims->batch, dims->vocab);
+  const PackJob pack = defer ? vocab_pack_job(vp, hidden, vws, arrivals, dims->batch) : PackJob{};
+  std::vector<CombineJob> merges;
+  st = run_attention(dims, q, k_pool, v_pool, kv_off, kv_len, scale, attn_out,
+                     static_cast<char*>(workspace) + tree_ws(dims), stm, ev[0], ev[1], parent, nullptr,
+                     defer ? &merges : nullptr, &pack);
+  if (st != SD_OK) return st;
   if (launch_vocab(dims->dtype, vp, hidden != nullptr ? hidden : attn_out, w_vocab, logits, vws, stm, ev[2], ev[3],
-                   accept_arrivals(acc_ws, dims->batch, dims->vocab), dims->batch) != hipSuccess)
+                   arrivals, dims->batch, pack.nblocks > 0) != hipSuccess)
     return SD_ERR_HIP;
   return run_accept_tree(dims, logits, row_lse, tokens, parent, u, kv_len, accept_len, out_tok, out_node,
                          new_kv_len, acc_ws, stm, ev[4], ev[5], defer ? &merges : nullptr,

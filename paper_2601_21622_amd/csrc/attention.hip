@@ -43,6 +43,7 @@
 #include "combine.h"
 #include "common.h"
 #include "launch.h"
+#include "pack.h"
 
 namespace sdv {
 
@@ -108,6 +109,34 @@ __device__ __forceinline__ bool key_visible(int key, int pend, uint64_t anc) {
 }
 
 __device__ __forceinline__ uint64_t chain_mask(int j) { return j >= 63 ? ~0ull : ((2ull << j) - 1ull); }
+
+// Tree verification: ancestor mask of position `lane` (< G; bit a: position a is
+// it, the root or an ancestor) of a request whose N = G - 1 nodes' parents are
+// at `parent` (node i's parent in [-1, i), -1 the root; anything else is taken
+// as the root).  Pointer jumping: six rounds join chains of up to 64 positions.
+// The whole wave takes part; rows then pick their position's mask by shuffle,
+// which costs a wave half a microsecond where masks from a launch of their own
+// cost the step 4.7.
+__device__ __forceinline__ uint64_t tree_position_mask(const int32_t* __restrict__ parent, int G) {
+  const int lane = threadIdx.x & 63;
+  int p = 0;
+  if (lane > 0 && lane < G) {
+    const int pp = parent[lane - 1];
+    p = (pp >= -1 && pp < lane - 1) ? pp + 1 : 0;
+  }
+  uint64_t m = 1ull | (1ull << lane);
+#pragma unroll
+  for (int i = 0; i < 6; ++i) {
+    const uint32_t lo = __shfl((uint32_t)m, p), hi = __shfl((uint32_t)(m >> 32), p);
+    m |= ((uint64_t)hi << 32) | lo;
+    p = __shfl(p, p);
+  }
+  return m;
+}
+__device__ __forceinline__ uint64_t shfl_mask(uint64_t m, int src) {
+  const uint32_t lo = __shfl((uint32_t)m, src), hi = __shfl((uint32_t)(m >> 32), src);
+  return ((uint64_t)hi << 32) | lo;
+}
 
 // Online softmax over a 32-key tile, in the log2 domain, for RB 16-row
 // blocks at once: in block rb the lane owns row lr and keys
@@ -556,17 +585,19 @@ __device__ __forceinline__ void write_partial(const AttnShape& s, const AttnBatc
 // Running state of rows row0 .. row0 + 16*RB - 1 of KV head g: Q fragments
 // (B operand of S^T = K Q^T; lane holds row row0 + rb*16 + lr, d = ds*32 +
 // lg*8 .. +8), causal limits, empty sums.  Rows past s.rows are padding.
-template <int RB, int D>
-__device__ __forceinline__ void init_rows(AttnRows<RB, D>& st, const AttnShape& s, const uint64_t* __restrict__ anc,
+template <int RB, int D, bool TREE>
+__device__ __forceinline__ void init_rows(AttnRows<RB, D>& st, const AttnShape& s, const int32_t* __restrict__ parent,
                                           const uint16_t* __restrict__ q, int req, int g, int L, int row0) {
   constexpr int DS = D / 32;
   constexpr int DB = D / 16;
   const int lane = threadIdx.x & 63;
   const int lr = lane & 15;
   const int lg = lane >> 4;
+  const uint64_t masks = TREE ? tree_position_mask(parent + (int64_t)req * (s.G - 1), s.G) : 0ull;
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
     const int row = row0 + rb * 16 + lr;
+    const uint64_t mask = TREE ? shfl_mask(masks, min(row, s.rows - 1) / s.group) : 0ull;
     if (row < s.rows) {
       const int j = row / s.group;
       const int h = g * s.group + (row - j * s.group);
@@ -574,7 +605,7 @@ __device__ __forceinline__ void init_rows(AttnRows<RB, D>& st, const AttnShape& 
 #pragma unroll
       for (int ds = 0; ds < DS; ++ds) st.qf[rb][ds] = load_bf16x8(qrow + ds * 32 + lg * 8);
       st.pend[rb] = L - s.G - 1;
-      st.anc[rb] = anc != nullptr ? anc[(int64_t)req * s.G + j] : chain_mask(j);
+      st.anc[rb] = mask;
       st.lim[rb] = L - s.G + j;
     } else {
 #pragma unroll
@@ -594,7 +625,11 @@ template <int RB, int D, bool TREE, bool PAGED>
 __global__ __launch_bounds__(kAttnThreads, 1)
 void attn_bf16_kernel(const AttnShape s, const AttnBatch bt, const uint16_t* __restrict__ q,
                       const uint16_t* __restrict__ kp, const uint16_t* __restrict__ vp,
-                      AttnPartials parts) {
+                      AttnPartials parts, const PackJob pj) {
+  if ((int)blockIdx.x >= pj.block0) {
+    pack_hidden_block(pj, blockIdx.x - pj.block0);
+    return;
+  }
   using T = Tile<D>;
   constexpr int kStage = kAttnWaves * T::kBytes;  // one stage of K or V, all waves
   // Two stages of K and V tiles.
@@ -618,7 +653,7 @@ void attn_bf16_kernel(const AttnShape s, const AttnBatch bt, const uint16_t* __r
 
   AttnRows<RB, D> st;
   const int row0 = __builtin_amdgcn_readfirstlane(rg * RB * 16);
-  init_rows<RB, D>(st, s, bt.anc, q, req, g, L, row0);
+  init_rows<RB, D, TREE>(st, s, bt.parent, q, req, g, L, row0);
 
   // Tile i of the item starts at key k_begin + 32i and is staged in stage
   // i & 1; tile i + 1 loads while tile i is folded in, its DMAs spread over
@@ -714,7 +749,11 @@ template <int RB, int D, bool TREE, bool PAGED>
 __global__ __launch_bounds__(kAttnThreads, (RB == 1 ? 2 : 1))
 void attn_bf16_reg_kernel(const AttnShape s, const AttnBatch bt, const uint16_t* __restrict__ q,
                           const uint16_t* __restrict__ kp, const uint16_t* __restrict__ vp,
-                          AttnPartials parts) {
+                          AttnPartials parts, const PackJob pj) {
+  if ((int)blockIdx.x >= pj.block0) {
+    pack_hidden_block(pj, blockIdx.x - pj.block0);
+    return;
+  }
   using T = Tile<D>;
   constexpr int NB = T::kBlocks;
   __shared__ __align__(1024) unsigned char ksm[kAttnWaves * T::kBytes];
@@ -737,7 +776,7 @@ void attn_bf16_reg_kernel(const AttnShape s, const AttnBatch bt, const uint16_t*
   const KVSrc<D, PAGED> src = kv_src<D, PAGED>(s, bt, kp, vp, b, g, L, k_begin);
 
   AttnRows<RB, D> st;
-  init_rows<RB, D>(st, s, bt.anc, q, req, g, L, 0);
+  init_rows<RB, D, TREE>(st, s, bt.parent, q, req, g, L, 0);
 
   const int ntiles = (k_end - k_begin + kTile - 1) / kTile;
   unsigned char* kt = ksm + wave * T::kBytes;
@@ -859,6 +898,7 @@ void attn_f32_kernel(const AttnShape s, const AttnBatch bt, const float* __restr
       }
   }
 
+  const uint64_t masks = bt.parent != nullptr ? tree_position_mask(bt.parent + (int64_t)req * (s.G - 1), s.G) : 0ull;
   for (int row0 = 0; row0 < s.rows; row0 += 16) {
     float m = kNegBig, l = 0.f;
     if (live) {
@@ -868,7 +908,7 @@ void attn_f32_kernel(const AttnShape s, const AttnBatch bt, const float* __restr
       f32x4 qf[KS];
 #pragma unroll
       for (int i = 0; i < KS; ++i) qf[i] = *reinterpret_cast<const f32x4*>(qr + i * 16);
-      const uint64_t anc = bt.anc != nullptr ? bt.anc[(int64_t)req * s.G + j] : chain_mask(j);
+      const uint64_t anc = bt.parent != nullptr ? shfl_mask(masks, j) : chain_mask(j);
       f32x4 sc[2][2];  // [key block][parity of the step]: two shorter chains round less than one
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb) sc[kb][0] = sc[kb][1] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -963,41 +1003,44 @@ void attn_combine_kernel(const AttnShape s, const AttnBatch bt, AttnPartials par
 
 template <int RB, int D, bool TREE, bool PAGED>
 hipError_t launch_bf16(const AttnShape& s, const AttnBatch& bt, int nchunks, const void* q, const void* k,
-                       const void* v, AttnPartials parts, hipStream_t stream, hipEvent_t e0, hipEvent_t e1) {
+                       const void* v, AttnPartials parts, PackJob pj, hipStream_t stream, hipEvent_t e0, hipEvent_t e1) {
   const int items = nchunks * s.Hkv * s.row_groups;
-  hipExtLaunchKernelGGL((attn_bf16_kernel<RB, D, TREE, PAGED>), dim3((items + kAttnWaves - 1) / kAttnWaves), dim3(kAttnThreads), 0,
+  pj.block0 = (items + kAttnWaves - 1) / kAttnWaves;
+  hipExtLaunchKernelGGL((attn_bf16_kernel<RB, D, TREE, PAGED>), dim3(pj.block0 + pj.nblocks), dim3(kAttnThreads), 0,
                         stream, e0, e1, 0, s, bt, static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
-                        static_cast<const uint16_t*>(v), parts);
+                        static_cast<const uint16_t*>(v), parts, pj);
   return hipGetLastError();
 }
 
 template <int RB, int D, bool TREE, bool PAGED>
 hipError_t launch_reg(const AttnShape& s, const AttnBatch& bt, int nchunks, const void* q, const void* k,
-                      const void* v, AttnPartials parts, hipStream_t stream, hipEvent_t e0, hipEvent_t e1) {
-  hipExtLaunchKernelGGL((attn_bf16_reg_kernel<RB, D, TREE, PAGED>), dim3((nchunks * s.Hkv + kAttnWaves - 1) / kAttnWaves),
-                        dim3(kAttnThreads), 0, stream, e0, e1, 0, s, bt, static_cast<const uint16_t*>(q),
-                        static_cast<const uint16_t*>(k), static_cast<const uint16_t*>(v), parts);
+                      const void* v, AttnPartials parts, PackJob pj, hipStream_t stream, hipEvent_t e0, hipEvent_t e1) {
+  pj.block0 = (nchunks * s.Hkv + kAttnWaves - 1) / kAttnWaves;
+  hipExtLaunchKernelGGL((attn_bf16_reg_kernel<RB, D, TREE, PAGED>), dim3(pj.block0 + pj.nblocks), dim3(kAttnThreads), 0,
+                        stream, e0, e1, 0, s, bt, static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
+                        static_cast<const uint16_t*>(v), parts, pj);
   return hipGetLastError();
 }
 
 template <int D, bool TREE, bool PAGED>
 hipError_t dispatch_rb(int rb, const AttnShape& s, const AttnBatch& bt, int nchunks, const void* q, const void* k,
-                       const void* v, AttnPartials parts, hipStream_t stream, hipEvent_t e0, hipEvent_t e1) {
+                       const void* v, AttnPartials parts, const PackJob& pj, hipStream_t stream, hipEvent_t e0,
+                       hipEvent_t e1) {
   switch (rb) {
-    case 1: return launch_reg<1, D, TREE, PAGED>(s, bt, nchunks, q, k, v, parts, stream, e0, e1);
-    case 2: return launch_bf16<2, D, TREE, PAGED>(s, bt, nchunks, q, k, v, parts, stream, e0, e1);
-    case 3: return launch_bf16<3, D, TREE, PAGED>(s, bt, nchunks, q, k, v, parts, stream, e0, e1);
-    case 4: return launch_bf16<4, D, TREE, PAGED>(s, bt, nchunks, q, k, v, parts, stream, e0, e1);
-    case 5: return launch_bf16<5, D, TREE, PAGED>(s, bt, nchunks, q, k, v, parts, stream, e0, e1);
+    case 1: return launch_reg<1, D, TREE, PAGED>(s, bt, nchunks, q, k, v, parts, pj, stream, e0, e1);
+    case 2: return launch_bf16<2, D, TREE, PAGED>(s, bt, nchunks, q, k, v, parts, pj, stream, e0, e1);
+    case 3: return launch_bf16<3, D, TREE, PAGED>(s, bt, nchunks, q, k, v, parts, pj, stream, e0, e1);
+    case 4: return launch_bf16<4, D, TREE, PAGED>(s, bt, nchunks, q, k, v, parts, pj, stream, e0, e1);
+    case 5: return launch_bf16<5, D, TREE, PAGED>(s, bt, nchunks, q, k, v, parts, pj, stream, e0, e1);
     default: break;
   }
   // Six to eight blocks per wave only at head dimension 64 (at 128 the rows
   // split over row groups first).
   if constexpr (D == 64) {
     switch (rb) {
-      case 6: return launch_bf16<6, D, TREE, PAGED>(s, bt, nchunks, q, k, v, parts, stream, e0, e1);
-      case 7: return launch_bf16<7, D, TREE, PAGED>(s, bt, nchunks, q, k, v, parts, stream, e0, e1);
-      case 8: return launch_bf16<8, D, TREE, PAGED>(s, bt, nchunks, q, k, v, parts, stream, e0, e1);
+      case 6: return launch_bf16<6, D, TREE, PAGED>(s, bt, nchunks, q, k, v, parts, pj, stream, e0, e1);
+      case 7: return launch_bf16<7, D, TREE, PAGED>(s, bt, nchunks, q, k, v, parts, pj, stream, e0, e1);
+      case 8: return launch_bf16<8, D, TREE, PAGED>(s, bt, nchunks, q, k, v, parts, pj, stream, e0, e1);
       default: break;
     }
   }
@@ -1036,24 +1079,6 @@ void tree_commit_kernel(CommitBatch cb, int G, int D, int esz, const int32_t* __
         *reinterpret_cast<u32x4*>(base + (int64_t)dst * row_bytes) = v;
       }
     }
-  }
-}
-
-// One workgroup per request, one thread per position: walk up the parents
-// (each step moves to a strictly smaller position, so at most g steps).
-__global__ __launch_bounds__(kWave)
-void tree_masks_kernel(int N, const int32_t* __restrict__ parent, uint64_t* __restrict__ masks) {
-  const int b = blockIdx.x;
-  const int G = N + 1;
-  for (int g = threadIdx.x; g < G; g += kWave) {
-    uint64_t m = 1ull;
-    int pos = g;
-    while (pos > 0) {
-      m |= 1ull << pos;
-      const int pp = parent[(int64_t)b * N + pos - 1];
-      pos = (pp >= -1 && pp < pos - 1) ? pp + 1 : 0;
-    }
-    masks[(int64_t)b * G + g] = m;
   }
 }
 
@@ -1136,9 +1161,11 @@ AttnPartials attn_carve(void* ws, int64_t total_chunks, int Hkv, int rows, int D
 
 hipError_t launch_attention(int dtype, const AttnShape& s, const AttnBatch& bt, int nchunks,
                             const void* q, const void* k, const void* v, AttnPartials parts,
-                            hipStream_t stream, hipEvent_t e0, hipEvent_t e1) {
+                            hipStream_t stream, hipEvent_t e0, hipEvent_t e1, const PackJob* pack) {
   if (nchunks <= 0) return hipSuccess;
+  const PackJob pj = pack != nullptr ? *pack : PackJob{};
   if (dtype == 0) {
+    if (pj.nblocks > 0) return hipErrorInvalidValue;  // only bf16 projections pack
     if (bt.pages != nullptr) return hipErrorInvalidValue;  // paged caches are bf16 only
     const auto kern = s.D == 128 ? attn_f32_kernel<128> : attn_f32_kernel<64>;
     hipExtLaunchKernelGGL(kern, dim3(nchunks, s.Hkv), dim3(kAttnThreads), 0, stream, e0, e1, 0, s, bt,
@@ -1148,18 +1175,18 @@ hipError_t launch_attention(int dtype, const AttnShape& s, const AttnBatch& bt, 
   // 16-row blocks per wave: a KV head's blocks split over its row groups.
   const int rb = ((s.rows + 15) / 16 + s.row_groups - 1) / s.row_groups;
   // Mask kinds: chain or tree; cache layouts: segments or pages (chain only).
-  const bool tree = bt.anc != nullptr;
+  const bool tree = bt.parent != nullptr;
   const bool paged = bt.pages != nullptr;
   if (tree && paged) return hipErrorInvalidValue;
   if (s.D == 128) {
-    if (paged) return dispatch_rb<128, false, true>(rb, s, bt, nchunks, q, k, v, parts, stream, e0, e1);
-    return tree ? dispatch_rb<128, true, false>(rb, s, bt, nchunks, q, k, v, parts, stream, e0, e1)
-                : dispatch_rb<128, false, false>(rb, s, bt, nchunks, q, k, v, parts, stream, e0, e1);
+    if (paged) return dispatch_rb<128, false, true>(rb, s, bt, nchunks, q, k, v, parts, pj, stream, e0, e1);
+    return tree ? dispatch_rb<128, true, false>(rb, s, bt, nchunks, q, k, v, parts, pj, stream, e0, e1)
+                : dispatch_rb<128, false, false>(rb, s, bt, nchunks, q, k, v, parts, pj, stream, e0, e1);
   }
   if (s.D == 64) {
-    if (paged) return dispatch_rb<64, false, true>(rb, s, bt, nchunks, q, k, v, parts, stream, e0, e1);
-    return tree ? dispatch_rb<64, true, false>(rb, s, bt, nchunks, q, k, v, parts, stream, e0, e1)
-                : dispatch_rb<64, false, false>(rb, s, bt, nchunks, q, k, v, parts, stream, e0, e1);
+    if (paged) return dispatch_rb<64, false, true>(rb, s, bt, nchunks, q, k, v, parts, pj, stream, e0, e1);
+    return tree ? dispatch_rb<64, true, false>(rb, s, bt, nchunks, q, k, v, parts, pj, stream, e0, e1)
+                : dispatch_rb<64, false, false>(rb, s, bt, nchunks, q, k, v, parts, pj, stream, e0, e1);
   }
   return hipErrorInvalidValue;
 }
@@ -1174,12 +1201,6 @@ hipError_t launch_attention_combine(int dtype, const AttnShape& s, const AttnBat
   else
     hipLaunchKernelGGL(attn_combine_kernel<uint16_t>, grid, dim3(kCombineThreads), 0, stream, s, bt, parts,
                        static_cast<uint16_t*>(out));
-  return hipGetLastError();
-}
-
-hipError_t launch_tree_masks(int B, int N, const int32_t* parent, uint64_t* masks, hipStream_t stream) {
-  if (B <= 0) return hipSuccess;
-  hipLaunchKernelGGL(tree_masks_kernel, dim3(B), dim3(kWave), 0, stream, N, parent, masks);
   return hipGetLastError();
 }
 

@@ -12,6 +12,10 @@ typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 typedef __attribute__((__vector_size__(2 * sizeof(uint32_t)))) uint32_t u32x2;
 
+// Four floats at 4-byte alignment: rows of a vocabulary that is no multiple of
+// four.  Global accesses of 16 bytes need dword alignment only.
+typedef f32x4 f32x4_u __attribute__((aligned(4)));
+
 constexpr int kWave = 64;
 // Finite stand-in for -infinity in running maxima: masked scores are -inf,
 // so exp2(-inf - m) is exactly 0 for any finite running maximum m.

@@ -18,16 +18,13 @@ struct AttnBatch {
   int32_t chunk_prefix[kMaxReqPerLaunch + 1];    // local chunk index where each request starts
   int32_t kv_len[kMaxReqPerLaunch];
   int64_t kv_off[kMaxReqPerLaunch];
-  const uint64_t* anc;  // tree verification: [B][G] ancestor masks (bit a: tail position a visible), or null
+  const int32_t* parent;  // tree verification: [B][G - 1] parents of the nodes, or null
   // Paged cache (kv_off unused): K and V pools [num_pages][Hkv][2^page_shift][D],
   // block table [B][max_pages] of page ids (clamped into [0, num_pages)), or null.
   const int32_t* pages;
   int32_t page_shift, max_pages, num_pages;
 };
 
-// Tree verification: ancestor masks [B][N + 1] from parents [B][N] (node i's
-// parent in [-1, i), -1 the root; anything else is taken as the root).
-hipError_t launch_tree_masks(int B, int N, const int32_t* parent, uint64_t* masks, hipStream_t stream);
 // Tree commit: in each request's cache move the accepted nodes' K/V rows next
 // to the root.
 struct CommitBatch {
@@ -66,10 +63,22 @@ int64_t attn_max_chunks(int dtype, int Hkv, int B, int64_t max_kv_len);
 size_t attn_partial_bytes(int64_t total_chunks, int Hkv, int rows, int D);
 AttnPartials attn_carve(void* ws, int64_t total_chunks, int Hkv, int rows, int D);
 
+// Repacking of the hidden rows that an attention launch carries for the
+// projection after it (nblocks 0: none); `clear` (nclear ints) is set to zero.
+struct PackJob {
+  int M, K;
+  const uint16_t* hidden;
+  uint16_t* out;
+  int* clear;
+  int nclear;
+  int nblocks;
+  int block0;  // set by the launcher: the first block after the attention's own
+};
+
 hipError_t launch_attention(int dtype, const AttnShape& s, const AttnBatch& batch, int nchunks,
                             const void* q, const void* k_pool, const void* v_pool,
                             AttnPartials parts, hipStream_t stream, hipEvent_t ev_start,
-                            hipEvent_t ev_stop);
+                            hipEvent_t ev_stop, const PackJob* pack = nullptr);
 hipError_t launch_attention_combine(int dtype, const AttnShape& s, const AttnBatch& batch,
                                     AttnPartials parts, void* out, hipStream_t stream);
 
@@ -95,9 +104,13 @@ hipError_t launch_pack_vocab(int K, int V, const void* w, void* out, hipStream_t
 size_t vocab_workspace_bytes(const VocabPlan& p);
 // `clear` (nclear ints, may be null) is set to zero by the launch: the
 // acceptance's arrival counters, for a fused acceptance launch that follows.
+// With `packed_hidden` an earlier launch carried vocab_pack_job's repacking (and
+// the clearing).
 hipError_t launch_vocab(int dtype, const VocabPlan& p, const void* hidden, const void* w,
                         float* logits, void* workspace, hipStream_t stream, hipEvent_t ev_start,
-                        hipEvent_t ev_stop, int* clear = nullptr, int nclear = 0);
+                        hipEvent_t ev_stop, int* clear = nullptr, int nclear = 0, bool packed_hidden = false);
+// The repacking launch_vocab would start with (nblocks 0 when it has none).
+PackJob vocab_pack_job(const VocabPlan& p, const void* hidden, void* workspace, int* clear, int nclear);
 constexpr int kLineMaxBlocks = 4;  // 16-row blocks per workgroup of the line schedule
 // The line schedule (lines.hip): a wave owns 16 vocabulary entries, a
 // workgroup p.mblocks 16-row blocks.  line_plan fills nbw, waves, mtiles and

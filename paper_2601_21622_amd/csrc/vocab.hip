@@ -37,6 +37,7 @@
 
 #include "common.h"
 #include "launch.h"
+#include "pack.h"
 #include "vocab_tile.h"
 
 namespace sdv {
@@ -135,7 +136,6 @@ __device__ __forceinline__ void tile_epilogue32(const f32x16 (&acc)[MB][NB], int
   const int lane = threadIdx.x & 63;
   const int j = lane & 31;
   const int h = lane >> 5;
-  const bool v4 = (V % 4) == 0;
   float tmax[MB];
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb) {
@@ -149,8 +149,8 @@ __device__ __forceinline__ void tile_epilogue32(const f32x16 (&acc)[MB][NB], int
         const f32x4 q = {acc[mb][nb][4 * g], acc[mb][nb][4 * g + 1], acc[mb][nb][4 * g + 2], acc[mb][nb][4 * g + 3]};
         if (m < M) {
           float* dst = logits + (int64_t)m * V + v0;
-          if (v4 && v0 + 3 < V) {
-            *reinterpret_cast<f32x4*>(dst) = q;
+          if (v0 + 3 < V) {
+            *reinterpret_cast<f32x4_u*>(dst) = q;
           } else {
 #pragma unroll
             for (int i = 0; i < 4; ++i)
@@ -460,7 +460,7 @@ __device__ __forceinline__ void tile_epilogue_wide(const f32x16 (&acc)[MB][NB], 
   const int lane = threadIdx.x & 63;
   const int j = lane & 31;
   const int h = lane >> 5;
-  const bool full = (V % 4) == 0 && (blk0 + NB) * 32 <= V;  // wave-uniform
+  const bool full = (blk0 + NB) * 32 <= V;  // wave-uniform
 #pragma unroll
   for (int mb = MB - 1; mb >= 0; --mb) {
     f32x16 av[NB];
@@ -476,7 +476,7 @@ __device__ __forceinline__ void tile_epilogue_wide(const f32x16 (&acc)[MB][NB], 
         const f32x4 q = {av[nb][4 * g], av[nb][4 * g + 1], av[nb][4 * g + 2], av[nb][4 * g + 3]};
         float* dst = logits + (int64_t)m * V + v0;
         if (full) {
-          if (m < M) *reinterpret_cast<f32x4*>(dst) = q;
+          if (m < M) *reinterpret_cast<f32x4_u*>(dst) = q;
           x = fmaxf(x, fmaxf(fmaxf(q[0], q[1]), fmaxf(q[2], q[3])));
         } else {
 #pragma unroll
@@ -680,26 +680,8 @@ void vocab_bf16_wide_kernel(int M, int K, int V, int ntiles, int mtiles, const u
   tile_epilogue_wide<MB, NB, NW>(acc, M, V, ntiles, tile, m0, blk0, logits, partials, red);
 }
 
-// Hidden rows [M][K] -> fragments [K/16][ceil(M/32)][64 lanes][8]: lane l of
-// fragment (k16, mb) holds row mb*32 + l%32, k 16*k16 + 8*(l/32) .. +8; rows
-// past M are zero.  One thread per 16-byte piece, writes coalesced.
-__global__ __launch_bounds__(kVThreads)
-void pack_hidden_kernel(int M, int K, const uint16_t* __restrict__ hidden, uint16_t* __restrict__ out,
-                        int* __restrict__ clear, int nclear) {
-  clear_counters(clear, nclear);
-  const int mbt = (M + 31) / 32;
-  const int64_t pieces = (int64_t)(K / 16) * mbt * 64;
-  for (int64_t i = (int64_t)blockIdx.x * kVThreads + threadIdx.x; i < pieces; i += (int64_t)gridDim.x * kVThreads) {
-    const int lane = (int)(i & 63);
-    const int64_t f = i >> 6;
-    const int mb = (int)(f % mbt);
-    const int k16 = (int)(f / mbt);
-    const int row = mb * 32 + (lane & 31);
-    u32x4 v = {0u, 0u, 0u, 0u};
-    if (row < M) v = *reinterpret_cast<const u32x4*>(hidden + (int64_t)row * K + k16 * 16 + (lane >> 5) * 8);
-    *reinterpret_cast<u32x4*>(out + i * 8) = v;
-  }
-}
+__global__ __launch_bounds__(kPackThreads)
+void pack_hidden_kernel(const PackJob j) { pack_hidden_block(j, blockIdx.x); }
 
 // One wave per row: maximum over tiles, then a float64 sum of the rescaled tile sums.
 __global__ __launch_bounds__(kVThreads)
@@ -730,15 +712,8 @@ void pack_vocab_kernel(int K, int V, const uint16_t* __restrict__ w, uint16_t* _
 }
 
 template <int MB, int NB, int NW, int S = (NW == 8 ? 3 : 6)>
-hipError_t launch_deep(const VocabPlan& p, const void* hidden, const void* w, float* logits, float2* partials,
-                       uint16_t* hpacked, hipStream_t stream, hipEvent_t e0, hipEvent_t e1, int* clear, int nclear) {
-  const int64_t pieces = (int64_t)(p.K / 16) * ((p.M + 31) / 32) * 64;
-  const int pblocks = (int)std::min<int64_t>((pieces + kVThreads - 1) / kVThreads, 4096);
-  // The events bracket the projection kernel alone (the repacking is a few
-  // microseconds of latency before it), so that they time the same launch a
-  // kernel trace lists.
-  hipExtLaunchKernelGGL(pack_hidden_kernel, dim3(pblocks), dim3(kVThreads), 0, stream, nullptr, nullptr, 0, p.M, p.K,
-                        static_cast<const uint16_t*>(hidden), hpacked, clear, nclear);
+hipError_t launch_deep(const VocabPlan& p, const void* w, float* logits, float2* partials,
+                       const uint16_t* hpacked, hipStream_t stream, hipEvent_t e0, hipEvent_t e1) {
   const dim3 grid((p.ntiles + 7) / 8 * 8 * p.mtiles), block(NW * kWave);
   const uint16_t* wv = static_cast<const uint16_t*>(w);
   if (p.packed)
@@ -751,12 +726,8 @@ hipError_t launch_deep(const VocabPlan& p, const void* hidden, const void* w, fl
 }
 
 template <int MB>
-hipError_t launch_wide(const VocabPlan& p, const void* hidden, const void* w, float* logits, float2* partials,
-                       uint16_t* hpacked, hipStream_t stream, hipEvent_t e0, hipEvent_t e1, int* clear, int nclear) {
-  const int64_t pieces = (int64_t)(p.K / 16) * ((p.M + 31) / 32) * 64;
-  const int pblocks = (int)std::min<int64_t>((pieces + kVThreads - 1) / kVThreads, 4096);
-  hipExtLaunchKernelGGL(pack_hidden_kernel, dim3(pblocks), dim3(kVThreads), 0, stream, nullptr, nullptr, 0, p.M, p.K,
-                        static_cast<const uint16_t*>(hidden), hpacked, clear, nclear);
+hipError_t launch_wide(const VocabPlan& p, const void* w, float* logits, float2* partials,
+                       const uint16_t* hpacked, hipStream_t stream, hipEvent_t e0, hipEvent_t e1) {
   const dim3 grid((p.ntiles + 7) / 8 * 8 * p.mtiles), block(4 * kWave);
   const uint16_t* wv = static_cast<const uint16_t*>(w);
   if (p.packed)
@@ -860,23 +831,46 @@ size_t vocab_workspace_bytes(const VocabPlan& p) {
   return b;
 }
 
+PackJob vocab_pack_job(const VocabPlan& p, const void* hidden, void* workspace, int* clear, int nclear) {
+  PackJob j{};
+  if (!p.deep) return j;
+  j.M = p.M;
+  j.K = p.K;
+  j.hidden = static_cast<const uint16_t*>(hidden);
+  j.out = reinterpret_cast<uint16_t*>(static_cast<char*>(workspace) + partial_bytes(p));
+  j.clear = clear;
+  j.nclear = clear != nullptr ? nclear : 0;
+  const int64_t pieces = (int64_t)(p.K / 16) * ((p.M + 31) / 32) * 64;
+  j.nblocks = (int)((pieces + kPackThreads * kPackEach - 1) / (kPackThreads * kPackEach));
+  return j;
+}
+
 hipError_t launch_vocab(int dtype, const VocabPlan& p, const void* hidden, const void* w, float* logits,
-                        void* workspace, hipStream_t stream, hipEvent_t e0, hipEvent_t e1, int* clear, int nclear) {
+                        void* workspace, hipStream_t stream, hipEvent_t e0, hipEvent_t e1, int* clear, int nclear,
+                        bool packed_hidden) {
   if (clear == nullptr) nclear = 0;
   float2* partials = static_cast<float2*>(workspace);
   uint16_t* hpacked = reinterpret_cast<uint16_t*>(static_cast<char*>(workspace) + partial_bytes(p));
   if (p.lines)
     return launch_vocab_lines(dtype == 0, p, hidden, w, logits, partials, stream, e0, e1, clear, nclear);
+  // The events bracket the projection kernel alone, so that they time the same
+  // launch a kernel trace lists.
+  if (!packed_hidden) {
+    const PackJob j = vocab_pack_job(p, hidden, workspace, clear, nclear);
+    hipLaunchKernelGGL(pack_hidden_kernel, dim3(j.nblocks), dim3(kPackThreads), 0, stream, j);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
 #define SDV_D(B, N, W) \
-  case B: return launch_deep<B, N, W>(p, hidden, w, logits, partials, hpacked, stream, e0, e1, clear, nclear);
+  case B: return launch_deep<B, N, W>(p, w, logits, partials, hpacked, stream, e0, e1);
   if (p.nbw == 2 * kWideNB) {
     switch (p.mblocks) {
-      case 2: return launch_wide<2>(p, hidden, w, logits, partials, hpacked, stream, e0, e1, clear, nclear);
-      case 3: return launch_wide<3>(p, hidden, w, logits, partials, hpacked, stream, e0, e1, clear, nclear);
-      case 4: return launch_wide<4>(p, hidden, w, logits, partials, hpacked, stream, e0, e1, clear, nclear);
-      case 5: return launch_wide<5>(p, hidden, w, logits, partials, hpacked, stream, e0, e1, clear, nclear);
-      case 6: return launch_wide<6>(p, hidden, w, logits, partials, hpacked, stream, e0, e1, clear, nclear);
-      case 7: return launch_wide<7>(p, hidden, w, logits, partials, hpacked, stream, e0, e1, clear, nclear);
+      case 2: return launch_wide<2>(p, w, logits, partials, hpacked, stream, e0, e1);
+      case 3: return launch_wide<3>(p, w, logits, partials, hpacked, stream, e0, e1);
+      case 4: return launch_wide<4>(p, w, logits, partials, hpacked, stream, e0, e1);
+      case 5: return launch_wide<5>(p, w, logits, partials, hpacked, stream, e0, e1);
+      case 6: return launch_wide<6>(p, w, logits, partials, hpacked, stream, e0, e1);
+      case 7: return launch_wide<7>(p, w, logits, partials, hpacked, stream, e0, e1);
       default: return hipErrorInvalidValue;
     }
   }

@@ -31,7 +31,6 @@ __device__ __forceinline__ void tile_epilogue(const f32x4 (&acc)[MBW][NBW], int 
   const int lane = threadIdx.x & 63;
   const int lr = lane & 15;
   const int lg = lane >> 4;
-  const bool v4 = (V % 4) == 0;
   float tmax[MBW];
 #pragma unroll
   for (int mb = 0; mb < MBW; ++mb) {
@@ -42,8 +41,8 @@ __device__ __forceinline__ void tile_epilogue(const f32x4 (&acc)[MBW][NBW], int 
       const int v0 = (blk0 + nb) * 16 + lg * 4;
       if (m < M) {
         float* dst = logits + (int64_t)m * V + v0;
-        if (v4 && v0 + 3 < V) {
-          *reinterpret_cast<f32x4*>(dst) = acc[mb][nb];
+        if (v0 + 3 < V) {
+          *reinterpret_cast<f32x4_u*>(dst) = acc[mb][nb];
         } else {
 #pragma unroll
           for (int i = 0; i < 4; ++i)
