@@ -131,6 +131,15 @@ __device__ __forceinline__ float wave_max(float v) {
   return fmaxf(fmaxf(lane_f32(v, 0), lane_f32(v, 16)), fmaxf(lane_f32(v, 32), lane_f32(v, 48)));
 }
 
+__device__ __forceinline__ uint64_t max_u64(uint64_t a, uint64_t b) { return a > b ? a : b; }
+__device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) {
+  v = max_u64(v, dpp_u64<kDppXor1>(v));
+  v = max_u64(v, dpp_u64<kDppXor2>(v));
+  v = max_u64(v, dpp_u64<kDppRowHalfMirror>(v));
+  v = max_u64(v, dpp_u64<kDppRowMirror>(v));
+  return max_u64(max_u64(lane_u64(v, 0), lane_u64(v, 16)), max_u64(lane_u64(v, 32), lane_u64(v, 48)));
+}
+
 __device__ __forceinline__ float wave_sum(float v) {
   v += dpp_f32<kDppXor1>(v);
   v += dpp_f32<kDppXor2>(v);
@@ -199,6 +208,22 @@ __device__ __forceinline__ float exp_diff(float a, float b) {
 __device__ __forceinline__ uint32_t order_key(float f) {
   const uint32_t b = __float_as_uint(f);
   return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
+}
+
+// The value of a key.
+__device__ __forceinline__ float key_value(uint32_t k) {
+  return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
+}
+
+// exp(t) for t <= 0, to about an ulp: 2^(t log2 e) on the hardware exponential,
+// with the product's rounding error (and log2 e's) put back to first order.
+// Half the instructions of expf, whose range checks t <= 0 does not need; the
+// pass over a row is bound by them.
+__device__ __forceinline__ float exp_neg(float t) {
+  const float h = t * kLog2e;
+  const float l = fmaf(t, 1.925963033500e-8f, fmaf(t, kLog2e, -h));  // log2 e = kLog2e + 1.92596e-8
+  const float e = __builtin_amdgcn_exp2f(h);
+  return fmaf(e, l * 0.693147180559945f, e);
 }
 
 // Workgroup barrier that orders LDS traffic only.  __syncthreads() also waits

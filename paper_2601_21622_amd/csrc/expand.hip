@@ -7,15 +7,20 @@
 // One workgroup of 1024 threads per frontier row (request b, node f).
 // Rank keys are the float32 order key of the logit, then the inverted token
 // id, so that equal logits rank by increasing id and every key is unique.
-//  1. Each wave scans its share of the row, 64 entries per step, keeping the
-//     k best keys seen so far sorted across its lanes (lane i: the i-th best).
-//     A ballot against the list's k-th key finds the few entries that enter
-//     it; each is placed by counting the better keys and shifting the rest
-//     down one lane.  The wave also keeps the row maximum.
-//  2. The waves' lists meet in LDS and wave 0 selects the k best of them the
-//     same way; the row maximum M is combined across waves.
-//  3. A second pass over the row (now in L2) sums exp(logit - M) in float64,
-//     giving lse; q(child) = exp(logit - lse) with the difference kept exact.
+//  1. Each wave scans its share of the row once, 32 steps of 64 entries loaded
+//     together (a 32,000-entry row in one round).  It keeps the k best keys
+//     seen so far sorted across its lanes (lane i: the i-th best): a ballot
+//     against the round's bound (the k-th largest of the lanes' maxima) and the
+//     list's k-th finds the few entries that may enter; each is placed by
+//     counting the better keys and shifting the rest down one lane.  From the same registers it keeps a running maximum m and,
+//     per lane in float64, the sum of exp(logit - m), rescaled when m moves.
+//  2. The waves' lists meet in LDS and wave 0 takes the k best of them one by
+//     one; the waves' sums, rescaled to the row maximum, are added in wave
+//     order, giving lse; q(child) = exp(logit - lse) with the difference kept
+//     exact, the logit taken from its key.
+// A row is one workgroup's, so a CU's inflow bounds it (128 KB take about 5
+// us); a second pass for the sums took as long again: 8 rows of 32,000 entries
+// 11.4 us against 20.4.
 // Children of node f are numbered first_child + f*k + j in rank order.
 #include <hip/hip_ext.h>
 
@@ -39,9 +44,10 @@ __device__ __forceinline__ uint64_t rank_key(float x, int v) {
 // Keys are unique and never 0 for a real entry.  Every cross-lane move is a
 // lane read (uniform source lane) or a one-lane DPP shift, so an insertion
 // costs no LDS round trip.
-__device__ __forceinline__ void offer(uint64_t key, int k, uint64_t& lst, uint64_t& thr) {
+// `may`: the lanes whose key may enter (the others' keys are not above thr).
+__device__ __forceinline__ void offer(unsigned long long may, uint64_t key, int k, uint64_t& lst, uint64_t& thr) {
   const int lane = threadIdx.x & 63;
-  unsigned long long cand = __ballot(key > thr);
+  unsigned long long cand = may;
   while (cand) {
     const int c = __ffsll(cand) - 1;
     cand &= cand - 1;
@@ -67,64 +73,88 @@ void expand_kernel(ExpandArgs e, const float* __restrict__ logits, int32_t* __re
   const int wave = threadIdx.x >> 6;
   const float* x = logits + (int64_t)row * e.V;
 
-  // 1. Wave lists and row maximum.
+  // 1. Wave lists, running maximum and sum.
   uint64_t lst = 0, thr = 0;
   float m = -INFINITY;
-  for (int base = wave * kWave; base < e.V; base += kExpThreads * kExpUnroll) {
-    float xs[kExpUnroll];
-#pragma unroll
-    for (int u = 0; u < kExpUnroll; ++u) xs[u] = x[min(base + u * kExpThreads + lane, e.V - 1)];
-#pragma unroll
-    for (int u = 0; u < kExpUnroll; ++u) {
-      const int v = base + u * kExpThreads + lane;
-      const bool in = v < e.V;
-      m = in ? fmaxf(m, xs[u]) : m;
-      offer(in ? rank_key(xs[u], v) : 0, e.k, lst, thr);
-    }
-  }
-  if (lane < kExpandMaxK) s_lst[wave][lane] = lane < e.k ? lst : 0;
-  const float mw = wave_max(m);
-  if (lane == 0) s_m[wave] = mw;
-  __syncthreads();
-  float M = s_m[0];
-#pragma unroll
-  for (int w = 1; w < kExpWaves; ++w) M = fmaxf(M, s_m[w]);
-
-  // 3. Sum of exp(logit - M), float64, fixed order.
   double acc = 0.0;
   for (int base = wave * kWave; base < e.V; base += kExpThreads * kExpUnroll) {
     float xs[kExpUnroll];
 #pragma unroll
     for (int u = 0; u < kExpUnroll; ++u) xs[u] = x[min(base + u * kExpThreads + lane, e.V - 1)];
+    float top = -INFINITY;  // this lane's largest entry of the round
+#pragma unroll
+    for (int u = 0; u < kExpUnroll; ++u) top = base + u * kExpThreads + lane < e.V ? fmaxf(top, xs[u]) : top;
+    // The k-th largest of the lanes' largest bounds the round's k-th largest
+    // from below (equal ones may fall together, which only lowers it).
+    float bound = top;
+    for (int j = 1; j < e.k; ++j) {
+      const float w = wave_max(bound);
+      bound = bound == w ? -INFINITY : bound;
+    }
+    bound = wave_max(bound);
 #pragma unroll
     for (int u = 0; u < kExpUnroll; ++u) {
-      const bool in = base + u * kExpThreads + lane < e.V;
-      acc += in && xs[u] != -INFINITY ? (double)expf(xs[u] - M) : 0.0;
+      // Within a step and from step to step indexes grow, so of equal logits
+      // the earlier ones are already listed: only larger order keys may enter.
+      const int v = base + u * kExpThreads + lane;
+      const bool in = v < e.V && xs[u] >= bound;
+      const unsigned long long may = __ballot(in && order_key(xs[u]) > (uint32_t)(thr >> 32));
+      if (may) offer(may, in ? rank_key(xs[u], v) : 0, e.k, lst, thr);
+    }
+    float mx = fmaxf(m, top);
+    mx = wave_max(mx);
+    if (mx == -INFINITY) continue;  // nothing finite yet: nothing to sum
+    if (mx > m) acc *= exp((double)m - (double)mx);
+    m = mx;
+#pragma unroll
+    for (int u = 0; u < kExpUnroll; ++u) {
+      const bool in = base + u * kExpThreads + lane < e.V && xs[u] != -INFINITY;
+      acc += in ? (double)exp_neg(xs[u] - m) : 0.0;
     }
   }
+  if (lane < kExpandMaxK) s_lst[wave][lane] = lane < e.k ? lst : 0;
   const double sw = wave_sum_f64(acc);
-  if (lane == 0) s_s[wave] = sw;
+  if (lane == 0) {
+    s_m[wave] = m;
+    s_s[wave] = sw;
+  }
   __syncthreads();
   if (wave != 0) return;
+  float M = s_m[0];
+#pragma unroll
+  for (int w = 1; w < kExpWaves; ++w) M = fmaxf(M, s_m[w]);
+  // Lane w rescales wave w's sum; the sums are added in wave order.
+  const double mine = lane < kExpWaves ? s_s[lane] * exp((double)s_m[lane] - (double)M) : 0.0;
   double S = 0.0;
 #pragma unroll
-  for (int w = 0; w < kExpWaves; ++w) S += s_s[w];
+  for (int w = 0; w < kExpWaves; ++w) S += lane_f64(mine, w);
   const float lse = (float)((double)M + log(S));
 
-  // 2. Wave 0 selects the k best of the waves' lists.
-  uint64_t best = 0, bthr = 0;
-  constexpr int kCand = kExpWaves * kExpandMaxK;
+  // 2. Wave 0 takes the k best of the waves' lists, largest first: four
+  // candidates per lane, keys unique.
+  constexpr int kCand = kExpWaves * kExpandMaxK / kWave;
+  uint64_t c[kCand];
 #pragma unroll
-  for (int i = 0; i < kCand / kWave; ++i) {
-    const int c = i * kWave + lane;
-    offer(s_lst[c / kExpandMaxK][c % kExpandMaxK], e.k, best, bthr);
+  for (int i = 0; i < kCand; ++i) {
+    const int n = i * kWave + lane;
+    c[i] = s_lst[n / kExpandMaxK][n % kExpandMaxK];
+  }
+  uint64_t best = 0;
+  for (int j = 0; j < e.k; ++j) {
+    uint64_t own = c[0];
+#pragma unroll
+    for (int i = 1; i < kCand; ++i) own = c[i] > own ? c[i] : own;
+    const uint64_t w = wave_max_u64(own);
+    best = lane == j ? w : best;
+#pragma unroll
+    for (int i = 0; i < kCand; ++i) c[i] = c[i] == w ? 0 : c[i];
   }
   if (lane < e.k) {
     const int v = (int)(0xffffffffu - (uint32_t)(best & 0xffffffffu));
     const int64_t o = (int64_t)b * e.N + e.first_child + f * e.k + lane;
     tokens[o] = v;
     parent[o] = e.frontier0 < 0 ? -1 : e.frontier0 + f;
-    q_child[o] = exp_diff(x[v], lse);
+    q_child[o] = exp_diff(key_value((uint32_t)(best >> 32)), lse);
   }
 }
 

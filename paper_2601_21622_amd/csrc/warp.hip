@@ -61,21 +61,6 @@ constexpr int kKeepMinV = 65536;
 constexpr int kKeepEach = 24;
 static_assert(kKeepEach * kWarpThreads >= kKeep, "one array serves both");
 
-__device__ __forceinline__ float key_value(uint32_t k) {
-  return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
-}
-
-// exp(t) for t <= 0, to about an ulp: 2^(t log2 e) on the hardware exponential,
-// with the product's rounding error (and log2 e's) put back to first order.
-// Half the instructions of expf, whose range checks t <= 0 does not need; the
-// pass over a row is bound by them.
-__device__ __forceinline__ float exp_neg(float t) {
-  const float h = t * kLog2e;
-  const float l = fmaf(t, 1.925963033500e-8f, fmaf(t, kLog2e, -h));  // log2 e = kLog2e + 1.92596e-8
-  const float e = __builtin_amdgcn_exp2f(h);
-  return fmaf(e, l * 0.693147180559945f, e);
-}
-
 // trunc(exp((x - m) / T) * 2^S) for x <= m, from the float32 value's bits (the
 // value is about 1 at most and S at most 62, so the shifts cover every case;
 // values below 2^-126 truncate to 0).
