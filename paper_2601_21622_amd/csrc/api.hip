@@ -764,6 +764,7 @@ const char* sd_vocab_kernel_name(const sd_dims_t* dims) {
   const VocabPlan p = vocab_plan(dims->dtype, dims->batch * (dims->gamma + 1), dims->hidden, dims->vocab,
                                  (dims->flags & SD_FLAG_PACKED_VOCAB) != 0);
   if (dims->dtype == SD_DTYPE_F32) return "vocab_f32_kernel";
+  if (p.rows) return "vocab_bf16_deep_kernel";  // the row-major form
   if (!p.deep) return "vocab_bf16_kernel";
   // The wide schedule is the deep shape with four 32-entry blocks per wave
   // on four waves (16-entry blocks per wave: 8).

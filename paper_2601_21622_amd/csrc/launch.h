@@ -94,6 +94,7 @@ struct VocabPlan {
   bool deep;       // bf16 deep-pipelined 32x32 schedule (more than 64 rows)
   bool packed;     // W in the fragment-order layout of launch_pack_vocab
   bool lines;      // line schedule (float32, or bf16 with few rows)
+  bool rows;       // row schedule (bf16, more rows, row-major W)
 };
 VocabPlan vocab_plan(int dtype, int M, int K, int V, bool packed);
 size_t vocab_packed_bytes(int K, int V);
@@ -119,6 +120,12 @@ void line_plan(int blocks, int V, VocabPlan* p);
 hipError_t launch_vocab_lines(bool f32, const VocabPlan& p, const void* hidden, const void* w, float* logits,
                               float2* partials, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop,
                               int* clear, int nclear);
+// The row schedule (rows.hip) for row-major W: takes a deep plan with four
+// waves of one or two 32-entry blocks (the tiles, and so the statistics, stay the
+// same) and sets its own M-tiles; false for the other shapes.
+bool rows_plan(int blocks32, VocabPlan* p);
+hipError_t launch_vocab_rows(const VocabPlan& p, const void* hidden, const void* w, float* logits, float2* partials,
+                             hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop, int* clear, int nclear);
 hipError_t launch_lse_combine(const VocabPlan& p, const float2* partials, float* row_lse,
                               hipStream_t stream);
 

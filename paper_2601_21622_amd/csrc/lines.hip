@@ -25,6 +25,7 @@
 #include <hip/hip_ext.h>
 
 #include <algorithm>
+#include <cmath>
 
 #include "common.h"
 #include "launch.h"
@@ -34,7 +35,6 @@ namespace sdv {
 
 namespace {
 
-constexpr int kLineBytes = 128;
 
 // Pipeline stages, at most eight: as many as fit half the CU's 160 KB (the
 // epilogue's few bytes aside) if that is three or more, so that two workgroups
@@ -51,18 +51,6 @@ __device__ __forceinline__ int line_unit(int l) { return ((l & 7) - ((l >> 3) & 
 __device__ __forceinline__ int line_read(int lane, int half) {
   const int q = (lane >> 3) & 1, r = lane & 7;
   return q * 1024 + r * 128 + ((4 * half + (lane >> 4) + (r & ~1)) & 7) * 16;
-}
-
-// DMA of one 1 KB block: lane l copies 16 bytes from g into LDS bytes lds +
-// 16l .. +15 (lds wave-uniform).  From inline assembly, so that the compiler
-// inserts no waits of its own between it and reads of other stages; the
-// kernel's vmcnt waits order it.  It sets M0 itself.
-template <bool NT>
-__device__ __forceinline__ void line_dma(const char* g, uint32_t lds) {
-  if (NT)
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off nt" : : "s"(lds), "v"(g) : "memory");
-  else
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds), "v"(g) : "memory");
 }
 
 // acc[mb][half] += W hidden^T over one line: w and h hold bytes 16*(lane/16)
@@ -229,14 +217,28 @@ void vocab_bf16_kernel(int M, int K, int V, int ntiles, int mtiles, const uint16
   vocab_lines<uint16_t, MB, NW, PACKED>(M, K, V, ntiles, mtiles, hidden, w, logits, partials);
 }
 
-// Waves per workgroup (16 vocabulary entries each): the most, since a
-// workgroup pulls the hidden lines once for all of its waves, that still give
-// most of the chip a workgroup.
-constexpr int kLineMinGroups = 192;
-int line_waves(int V, int mtiles) {
-  for (int nw = 8; nw > 2; nw /= 2)
-    if ((V + 16 * nw - 1) / (16 * nw) * mtiles >= kLineMinGroups) return nw;
-  return 2;
+// Waves per workgroup (16 vocabulary entries each), one to eight: the least
+// cost by the lines that the busiest of 256 CUs pulls, its workgroups' entries
+// and hidden rows, with 16 lines for a workgroup's start and end, and one and a
+// half times the hidden lines of the average CU on top (every workgroup asks
+// for the same ones at the same time).  Ties go to more waves.  Fitted to
+// measured kernels: 32 x 5120 x 20000 takes 31 us with five waves (250
+// workgroups), 40 with eight (157); 52 x 6400 x 10687 47 with four, 51 with
+// three or two; 8 x 1504 x 115716 54 with eight, 60 with six.
+constexpr int kLineMaxWaves = 8;
+int line_waves(int V, int mtiles, int mblocks) {
+  int best = kLineMaxWaves;
+  double least = 0.0;
+  for (int nw = kLineMaxWaves; nw >= 1; --nw) {
+    const double groups = (double)((V + 16 * nw - 1) / (16 * nw)) * mtiles;
+    const double rows = 16.0 * mblocks;
+    const double cost = std::ceil(groups / 256.0) * (16 * nw + rows + 16) + 1.5 * rows * groups / 256.0;
+    if (nw == kLineMaxWaves || cost < least) {
+      least = cost;
+      best = nw;
+    }
+  }
+  return best;
 }
 
 // Workgroups of a (vocabulary tile, M-tile) grid: one per tile, or groups of
@@ -273,8 +275,13 @@ hipError_t line_type(bool f32, const LineCall& a) {
 template <int MB>
 hipError_t line_waves_of(bool f32, const LineCall& a) {
   switch (a.p.waves) {
+    case 1: return line_type<MB, 1>(f32, a);
     case 2: return line_type<MB, 2>(f32, a);
+    case 3: return line_type<MB, 3>(f32, a);
     case 4: return line_type<MB, 4>(f32, a);
+    case 5: return line_type<MB, 5>(f32, a);
+    case 6: return line_type<MB, 6>(f32, a);
+    case 7: return line_type<MB, 7>(f32, a);
     case 8: return line_type<MB, 8>(f32, a);
     default: return hipErrorInvalidValue;
   }
@@ -286,7 +293,7 @@ void line_plan(int blocks, int V, VocabPlan* p) {
   p->nbw = 1;
   p->mtiles = (blocks + kLineMaxBlocks - 1) / kLineMaxBlocks;
   p->mblocks = (blocks + p->mtiles - 1) / p->mtiles;
-  p->waves = line_waves(V, p->mtiles);
+  p->waves = line_waves(V, p->mtiles, p->mblocks);
 }
 
 hipError_t launch_vocab_lines(bool f32, const VocabPlan& p, const void* hidden, const void* w, float* logits,

@@ -114,90 +114,6 @@ struct Deep32Cfg {
   static_assert(kOpsPerChunk <= kMfmas, "memory operations ride between MFMAs");
 };
 
-// Fixed-order combination of the NW per-wave values of row r.
-template <int NW, int R>
-__device__ __forceinline__ float waves_max(const float (*red)[R], int r) {
-  float x = fmaxf(fmaxf(red[0][r], red[1][r]), fmaxf(red[2][r], red[3][r]));
-  if (NW == 8) x = fmaxf(x, fmaxf(fmaxf(red[4][r], red[5][r]), fmaxf(red[6][r], red[7][r])));
-  return x;
-}
-template <int NW, int R>
-__device__ __forceinline__ float waves_sum(const float (*red)[R], int r) {
-  float x = (red[0][r] + red[1][r]) + (red[2][r] + red[3][r]);
-  if (NW == 8) x += (red[4][r] + red[5][r]) + (red[6][r] + red[7][r]);
-  return x;
-}
-
-template <int MB, int NB, int NW>
-__device__ __forceinline__ void tile_epilogue32(const f32x16 (&acc)[MB][NB], int M, int V, int ntiles, int tile,
-                                                int m0, int blk0, float* __restrict__ logits,
-                                                float2* __restrict__ partials, float (*red)[MB * 32]) {
-  const int wave = threadIdx.x >> 6;
-  const int lane = threadIdx.x & 63;
-  const int j = lane & 31;
-  const int h = lane >> 5;
-  float tmax[MB];
-#pragma unroll
-  for (int mb = 0; mb < MB; ++mb) {
-    const int m = m0 + mb * 32 + j;
-    float x = -INFINITY;
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int v0 = (blk0 + nb) * 32 + 8 * g + 4 * h;
-        const f32x4 q = {acc[mb][nb][4 * g], acc[mb][nb][4 * g + 1], acc[mb][nb][4 * g + 2], acc[mb][nb][4 * g + 3]};
-        if (m < M) {
-          float* dst = logits + (int64_t)m * V + v0;
-          if (v0 + 3 < V) {
-            *reinterpret_cast<f32x4_u*>(dst) = q;
-          } else {
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-              if (v0 + i < V) dst[i] = q[i];
-          }
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) x = (v0 + i < V) ? fmaxf(x, q[i]) : x;
-      }
-    }
-    x = fmaxf(x, __shfl_xor(x, 32));
-    if (h == 0) red[wave][mb * 32 + j] = x;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int mb = 0; mb < MB; ++mb) {
-    const int r = mb * 32 + j;
-    tmax[mb] = waves_max<NW, MB * 32>(red, r);
-  }
-  __syncthreads();
-#pragma unroll
-  for (int mb = 0; mb < MB; ++mb) {
-    float sm = 0.f;
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int v = (blk0 + nb) * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
-        sm += (v < V) ? expf(acc[mb][nb][r] - tmax[mb]) : 0.f;
-      }
-    sm += __shfl_xor(sm, 32);
-    if (h == 0) red[wave][mb * 32 + j] = sm;
-  }
-  __syncthreads();
-  if (wave == 0 && h == 0) {
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-      const int r = mb * 32 + j;
-      const int m = m0 + r;
-      if (m < M) {
-        const float sm = waves_sum<NW, MB * 32>(red, r);
-        partials[(int64_t)m * ntiles + tile] = make_float2(tmax[mb], sm);
-      }
-    }
-  }
-}
-
 template <int MB, int NB, int S, int NW, bool PACKED>
 __global__ __launch_bounds__(NW * kWave, 1)
 void vocab_bf16_deep_kernel(int M, int K, int V, int ntiles, int mtiles, const uint16_t* __restrict__ hpacked,
@@ -786,6 +702,7 @@ VocabPlan vocab_plan(int dtype, int M, int K, int V, bool packed) {
   VocabPlan p;
   p.packed = packed;
   p.lines = false;
+  p.rows = false;
   p.M = M;
   p.K = K;
   p.V = V;
@@ -814,6 +731,12 @@ VocabPlan vocab_plan(int dtype, int M, int K, int V, bool packed) {
         p.mtiles = mt;
         p.mblocks = mb;
       }
+    }
+    // Row-major W in tiles that the row schedule has: whole lines there
+    // (320 x 4096 x 32000: 217 us with the deep schedule's loads).
+    if (!packed && rows_plan(blocks32, &p)) {
+      p.rows = true;
+      p.deep = false;
     }
   }
   p.tile_n = 16 * p.waves * p.nbw;
@@ -851,6 +774,7 @@ hipError_t launch_vocab(int dtype, const VocabPlan& p, const void* hidden, const
   if (clear == nullptr) nclear = 0;
   float2* partials = static_cast<float2*>(workspace);
   uint16_t* hpacked = reinterpret_cast<uint16_t*>(static_cast<char*>(workspace) + partial_bytes(p));
+  if (p.rows) return launch_vocab_rows(p, hidden, w, logits, partials, stream, e0, e1, clear, nclear);
   if (p.lines)
     return launch_vocab_lines(dtype == 0, p, hidden, w, logits, partials, stream, e0, e1, clear, nclear);
   // The events bracket the projection kernel alone, so that they time the same

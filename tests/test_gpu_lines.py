@@ -1,6 +1,6 @@
 """GPU parity of the projection's line schedule (float32, and bfloat16 with at
-most 64 rows): every row-block count, two, four and eight waves per workgroup
-(chosen from the vocabulary), M-tiles of float32 past 64 rows, rows and
+most 64 rows): every row-block count, every number of waves per
+workgroup (chosen from the sizes), M-tiles of float32 past 64 rows, rows and
 vocabularies off every tile, K from one half line (bfloat16: 32 entries) past
 the pipeline's depth, odd numbers of half lines, row-major and packed weights.
 
@@ -27,6 +27,9 @@ CASES = [
     ("bf16", (1, 17), 96, 3001, False), ("bf16", (1, 17), 96, 3001, True), ("bf16", (8, 6), 352, 12301, False),
     ("bf16", (8, 6), 352, 12301, True), ("bf16", (7, 7), 1312, 24700, False), ("bf16", (7, 7), 1312, 24700, True),
     ("bf16", (16, 4), 1504, 24703, False), ("bf16", (16, 4), 512, 65, True),
+    # Vocabularies that take each wave count at 16 and 64 rows.
+    *[("bf16", (2, 4), 96, 16 * nw * 250 + 5, nw % 2 == 0) for nw in range(1, 9)],
+    *[("f32", (16, 4), 64, 16 * nw * 250 - 3, False) for nw in range(1, 9)],
 ]
 
 
