@@ -27,6 +27,9 @@ CASES = [
     ("bf16", (1, 17), 96, 3001, False), ("bf16", (1, 17), 96, 3001, True), ("bf16", (8, 6), 352, 12301, False),
     ("bf16", (8, 6), 352, 12301, True), ("bf16", (7, 7), 1312, 24700, False), ("bf16", (7, 7), 1312, 24700, True),
     ("bf16", (16, 4), 1504, 24703, False), ("bf16", (16, 4), 512, 65, True),
+    # Rows a multiple of 4 KB apart: the tiles start on different lines.
+    ("bf16", (3, 2), 2048, 4001, False), ("bf16", (3, 2), 2048, 4001, True), ("bf16", (8, 6), 4096, 2500, False),
+    ("f32", (2, 3), 1024, 3000, False), ("f32", (20, 4), 1024, 700, False),
     # Vocabularies that take each wave count at 16 and 64 rows.
     *[("bf16", (2, 4), 96, 16 * nw * 250 + 5, nw % 2 == 0) for nw in range(1, 9)],
     *[("f32", (16, 4), 64, 16 * nw * 250 - 3, False) for nw in range(1, 9)],
