@@ -12,8 +12,9 @@
 //     seen so far sorted across its lanes (lane i: the i-th best): a ballot
 //     against the round's bound (the k-th largest of the lanes' maxima) and the
 //     list's k-th finds the few entries that may enter; each is placed by
-//     counting the better keys and shifting the rest down one lane.  From the same registers it keeps a running maximum m and,
-//     per lane in float64, the sum of exp(logit - m), rescaled when m moves.
+//     counting the better keys and shifting the rest down one lane.  From the
+//     same registers it keeps a running maximum m and, per lane in float64, the
+//     sum of exp(logit - m), rescaled when m moves.
 //  2. The waves' lists meet in LDS and wave 0 takes the k best of them one by
 //     one; the waves' sums, rescaled to the row maximum, are added in wave
 //     order, giving lse; q(child) = exp(logit - lse) with the difference kept
@@ -94,16 +95,15 @@ void expand_kernel(ExpandArgs e, const float* __restrict__ logits, int32_t* __re
     bound = wave_max(bound);
 #pragma unroll
     for (int u = 0; u < kExpUnroll; ++u) {
-      // Within a step and from step to step indexes grow, so of equal logits
-      // the earlier ones are already listed: only larger order keys may enter.
       const int v = base + u * kExpThreads + lane;
-      const bool in = v < e.V && xs[u] >= bound;
-      const unsigned long long may = __ballot(in && order_key(xs[u]) > (uint32_t)(thr >> 32));
-      if (may) offer(may, in ? rank_key(xs[u], v) : 0, e.k, lst, thr);
+      // NaNs pass the bound: they rank by their keys like any other entry.
+      const bool in = v < e.V && !(xs[u] < bound);
+      const uint64_t key = in ? rank_key(xs[u], v) : 0;
+      const unsigned long long may = __ballot(key > thr);
+      if (may) offer(may, key, e.k, lst, thr);
     }
     float mx = fmaxf(m, top);
     mx = wave_max(mx);
-    if (mx == -INFINITY) continue;  // nothing finite yet: nothing to sum
     if (mx > m) acc *= exp((double)m - (double)mx);
     m = mx;
 #pragma unroll

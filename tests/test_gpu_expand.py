@@ -134,3 +134,28 @@ def test_expand_masked_children():
     masked = np.isin(to_np(tok)[:, sl], [2, 7])
     assert np.all(gq[:, sl][masked] == 0.0) and np.all(rq[:, sl][masked] == 0.0)
     assert np.all(np.abs(gq[:, sl] - rq[:, sl]) <= 2e-6 * rq[:, sl] + 1e-30)
+
+
+@pytest.mark.parametrize("V", [40, 3001, 40000])
+def test_expand_nan_logits_stay_ranked(V):
+    """NaN logits rank by their order keys (a quiet NaN above every number), as
+    the oracle ranks them: a row with a few, and one of nothing else, still
+    get k different tokens of the vocabulary, with a NaN probability."""
+    rng = np.random.default_rng(V)
+    k = 4
+    x = (rng.standard_normal((2, 2, V)) * 2.0).astype(np.float32)
+    x[0, 0, [3, V - 1]] = np.nan
+    x[1, 1, :] = np.nan
+    N = 2 + 2 * k
+    tok, par, q = _run_layer(x, k, 0, 2, N)
+    torch.cuda.synchronize()
+    with np.errstate(all="ignore"):
+        rt, rp, rq = expand_layer(x, k, 0, 2, N)
+    assert np.array_equal(to_np(tok), rt)
+    assert np.array_equal(to_np(par), rp)
+    gq = to_np(q).reshape(2, N)
+    for b, f in ((0, 0), (1, 1)):
+        assert np.all(np.isnan(gq[b, 2 + f * k:2 + (f + 1) * k]))
+    for b, f in ((0, 1), (1, 0)):
+        sl = slice(2 + f * k, 2 + (f + 1) * k)
+        assert np.all(np.abs(gq[b, sl] - rq[b, sl]) <= 2e-6 * rq[b, sl])
