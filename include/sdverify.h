@@ -137,8 +137,8 @@ SD_API int sd_verify_attention_tree(const sd_dims_t* dims, const void* q, const 
 
 /*
  * Repacked vocabulary weights.  The projection streams W once per step; in
- * the [V][hidden] layout every MFMA operand load touches 16 rows 2*hidden
- * bytes apart.  sd_pack_vocab rewrites W once (at weight-load time) into
+ * the [V][hidden] layout the rows it reads together lie 2*hidden bytes
+ * apart.  sd_pack_vocab rewrites W once (at weight-load time) into
  * fragment order, [hidden/32][ceil(V/16)][64 lanes][8 bf16]: fragment (s, n)
  * holds, for lane l, W[16n + l%16][32s + 8(l/16) .. +8], rows past V zero.
  * Each operand load is then 1 KB contiguous, and at every k-step the whole
@@ -205,8 +205,9 @@ SD_API int sd_accept_resample(const sd_dims_t* dims, const float* logits_or_prob
  *   kernel_events  (host) NULL, or 6 hipEvent_t handles (created with timing
  *                  enabled): start/stop of the attention kernel (without its
  *                  combine), of the vocabulary projection kernel (for more
- *                  than 64 rows the hidden repacking launch before it is
- *                  outside the pair) and
+ *                  than 64 rows and packed weights the hidden rows are
+ *                  repacked before it, outside the pair: by the attention
+ *                  launch's last workgroups, or by a launch of its own) and
  *                  of the acceptance (one launch in a step: the segment sums,
  *                  then the draw by the last workgroup of each request).
  *                  They are recorded by the kernel

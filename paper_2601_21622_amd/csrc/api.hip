@@ -88,10 +88,14 @@ size_t attention_ws(const sd_dims_t* d, int64_t chunks) {
 // position; the kernels derive the ancestor masks themselves).
 size_t tree_ws(const sd_dims_t* d) { return align_up(sizeof(uint64_t) * static_cast<size_t>(d->batch) * (d->gamma + 1)); }
 
-size_t logits_ws(const sd_dims_t* d) {
-  const VocabPlan p = vocab_plan(d->dtype, d->batch * (d->gamma + 1), d->hidden, d->vocab, (d->flags & SD_FLAG_PACKED_VOCAB) != 0);
-  return align_up(vocab_workspace_bytes(p));
+// The projection's plan; `small`: the one whose statistics take the least
+// workspace, for a caller whose workspace does not hold the other's.
+VocabPlan logits_plan(const sd_dims_t* d, bool small = false) {
+  return vocab_plan(d->dtype, d->batch * (d->gamma + 1), d->hidden, d->vocab, (d->flags & SD_FLAG_PACKED_VOCAB) != 0,
+                    small);
 }
+
+size_t logits_ws(const VocabPlan& p) { return align_up(vocab_workspace_bytes(p)); }
 
 int log2_exact(int v) {
   int k = 0;
@@ -186,9 +190,8 @@ int run_attention(const sd_dims_t* d, const void* q, const void* k, const void* 
   return SD_OK;
 }
 
-int run_logits(const sd_dims_t* d, const void* hidden, const void* w, float* logits, float* row_lse, void* ws,
+int run_logits(const sd_dims_t* d, const VocabPlan& p, const void* hidden, const void* w, float* logits, float* row_lse, void* ws,
                hipStream_t stream, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr) {
-  const VocabPlan p = vocab_plan(d->dtype, d->batch * (d->gamma + 1), d->hidden, d->vocab, (d->flags & SD_FLAG_PACKED_VOCAB) != 0);
   float2* partials = static_cast<float2*>(ws);
   hipError_t e = launch_vocab(d->dtype, p, hidden, w, logits, ws, stream, ev_start, ev_stop);
   if (e == hipSuccess) e = launch_lse_combine(p, partials, row_lse, stream);
@@ -315,11 +318,17 @@ size_t step_attention_ws(const sd_dims_t* dims, const int32_t* kv_len, float sca
 // attention merge rides in the acceptance's last launch and its partials
 // keep their own region: [partials][projection][acceptance].  Otherwise the
 // stages reuse one region in stream order.
-size_t step_ws(const sd_dims_t* dims, const int32_t* kv_len, float scale, const void* hidden,
-               const sd_kv_pages_t* pages) {
-  const size_t attn_bytes = step_attention_ws(dims, kv_len, scale, pages);
-  return hidden != nullptr ? attn_bytes + logits_ws(dims) + accept_stage_ws(dims)
-                           : std::max(attn_bytes, logits_ws(dims) + accept_stage_ws(dims));
+size_t step_ws(const sd_dims_t* dims, const VocabPlan& vp, size_t attn_bytes, bool side_by_side) {
+  const size_t rest = logits_ws(vp) + accept_stage_ws(dims);
+  return side_by_side ? attn_bytes + rest : std::max(attn_bytes, rest);
+}
+
+// The projection's plan for a step in `workspace_bytes`; false: none fits.
+bool step_plan(const sd_dims_t* dims, size_t attn_bytes, bool side_by_side, size_t workspace_bytes, VocabPlan* vp) {
+  *vp = logits_plan(dims);
+  if (workspace_bytes >= step_ws(dims, *vp, attn_bytes, side_by_side)) return true;
+  *vp = logits_plan(dims, true);
+  return workspace_bytes >= step_ws(dims, *vp, attn_bytes, side_by_side);
 }
 
 }  // namespace
@@ -329,7 +338,7 @@ extern "C" {
 size_t sd_workspace_bytes(const sd_dims_t* dims, int32_t max_kv_len) {
   if (check_dims(dims) != SD_OK || max_kv_len < dims->gamma + 1) return 0;
   const int64_t chunks = attn_max_chunks(dims->dtype, dims->n_kv_heads, dims->batch, max_kv_len);
-  return std::max({tree_ws(dims) + attention_ws(dims, chunks) + logits_ws(dims) + accept_stage_ws(dims),
+  return std::max({tree_ws(dims) + attention_ws(dims, chunks) + logits_ws(logits_plan(dims)) + accept_stage_ws(dims),
                    rate_ws(dims)});
 }
 
@@ -380,8 +389,10 @@ int sd_verify_logits(const sd_dims_t* dims, const void* hidden, const void* w_vo
   if (!aligned(hidden, 16) || !aligned(w_vocab, 16) || !aligned(logits, 16) || !aligned(row_lse, 4) ||
       !aligned(workspace, 16))
     return SD_ERR_INVALID_ARGUMENT;
-  if (workspace_bytes < logits_ws(dims)) return SD_ERR_WORKSPACE;
-  return run_logits(dims, hidden, w_vocab, logits, row_lse, workspace, static_cast<hipStream_t>(stream));
+  VocabPlan p = logits_plan(dims);
+  if (workspace_bytes < logits_ws(p)) p = logits_plan(dims, true);
+  if (workspace_bytes < logits_ws(p)) return SD_ERR_WORKSPACE;
+  return run_logits(dims, p, hidden, w_vocab, logits, row_lse, workspace, static_cast<hipStream_t>(stream));
 }
 
 int sd_accept_resample(const sd_dims_t* dims, const float* logits_or_probs, const float* row_lse,
@@ -471,7 +482,9 @@ int verify_step(const sd_dims_t* dims, const void* q, const void* k_pool, const 
   if (st != SD_OK) return st;
   const bool defer = hidden != nullptr;
   const size_t base = defer ? step_attention_ws(dims, kv_len, scale, pages) : 0;
-  if (workspace_bytes < step_ws(dims, kv_len, scale, hidden, pages)) return SD_ERR_WORKSPACE;
+  VocabPlan vp;
+  if (!step_plan(dims, step_attention_ws(dims, kv_len, scale, pages), defer, workspace_bytes, &vp))
+    return SD_ERR_WORKSPACE;
 
   hipEvent_t ev[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
   if (kernel_events != nullptr)
@@ -481,12 +494,11 @@ int verify_step(const sd_dims_t* dims, const void* q, const void* k_pool, const 
   // sums after them, since the fold reads the former while the segment kernel
   // writes the latter.
   void* vws = static_cast<char*>(workspace) + base;
-  const VocabPlan vp = vocab_plan(dims->dtype, dims->batch * (dims->gamma + 1), dims->hidden, dims->vocab, (dims->flags & SD_FLAG_PACKED_VOCAB) != 0);
   float2* partials = static_cast<float2*>(vws);
   // The projection's launches (or the repacking that the attention launch
   // carries) clear the acceptance's arrival counters, so the acceptance runs
   // as one launch.
-  void* acc_ws = static_cast<char*>(vws) + logits_ws(dims);
+  void* acc_ws = static_cast<char*>(vws) + logits_ws(vp);
   int* arrivals = accept_arrivals(acc_ws, dims->batch, dims->vocab);
   const PackJob pack = defer ? vocab_pack_job(vp, hidden, vws, arrivals, dims->batch) : PackJob{};
   std::vector<CombineJob> merges;
@@ -555,18 +567,16 @@ int sd_verify_step_sampled(const sd_dims_t* dims, const sd_sampling_t* sampling,
   // its partials in a region of their own; a workspace that only holds the
   // stages one after another gets the merge as a launch of its own.
   const size_t attn_bytes = step_attention_ws(dims, kv_len, scale, nullptr);
-  const size_t rest = logits_ws(dims) + accept_stage_ws(dims);
-  if (workspace_bytes < std::max(attn_bytes, rest)) return SD_ERR_WORKSPACE;
-  const bool defer = hidden != nullptr && workspace_bytes >= attn_bytes + rest;
+  VocabPlan vp;
+  if (!step_plan(dims, attn_bytes, false, workspace_bytes, &vp)) return SD_ERR_WORKSPACE;
+  const bool defer = hidden != nullptr && workspace_bytes >= step_ws(dims, vp, attn_bytes, true);
 
   hipEvent_t ev[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
   if (kernel_events != nullptr)
     for (int i = 0; i < 6; ++i) ev[i] = static_cast<hipEvent_t>(kernel_events[i]);
   hipStream_t stm = static_cast<hipStream_t>(stream);
-  const VocabPlan vp = vocab_plan(dims->dtype, dims->batch * (dims->gamma + 1), dims->hidden, dims->vocab,
-                                  (dims->flags & SD_FLAG_PACKED_VOCAB) != 0);
   void* vws = static_cast<char*>(workspace) + (defer ? attn_bytes : 0);
-  void* acc_ws = static_cast<char*>(vws) + logits_ws(dims);
+  void* acc_ws = static_cast<char*>(vws) + logits_ws(vp);
   int* arrivals = accept_arrivals(acc_ws, dims->batch, dims->vocab);
   const PackJob pack = defer ? vocab_pack_job(vp, hidden, vws, arrivals, dims->batch) : PackJob{};
   std::vector<CombineJob> merges;
@@ -634,9 +644,8 @@ int sd_verify_step_tree(const sd_dims_t* dims, const void* q, const void* k_pool
   // [reserved][partials][projection][acceptance].
   const bool defer = hidden != nullptr;
   const size_t base = defer ? attn_bytes : 0;
-  const size_t need = defer ? attn_bytes + logits_ws(dims) + accept_stage_ws(dims)
-                            : std::max(attn_bytes, logits_ws(dims) + accept_stage_ws(dims));
-  if (workspace_bytes < need) return SD_ERR_WORKSPACE;
+  VocabPlan vp;
+  if (!step_plan(dims, attn_bytes, defer, workspace_bytes, &vp)) return SD_ERR_WORKSPACE;
 
   hipEvent_t ev[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
   if (kernel_events != nullptr)
@@ -645,9 +654,7 @@ int sd_verify_step_tree(const sd_dims_t* dims, const void* q, const void* k_pool
   void* vws = static_cast<char*>(workspace) + base;
   // The walk launch folds the row log-sum-exps from the projection's
   // statistics, and the final draw runs as one launch.
-  const VocabPlan vp = vocab_plan(dims->dtype, dims->batch * (dims->gamma + 1), dims->hidden, dims->vocab,
-                                  (dims->flags & SD_FLAG_PACKED_VOCAB) != 0);
-  void* acc_ws = static_cast<char*>(vws) + logits_ws(dims);
+  void* acc_ws = static_cast<char*>(vws) + logits_ws(vp);
   int* arrivals = accept_arrivals(acc_ws, dims->batch, dims->vocab);
   const PackJob pack = defer ? vocab_pack_job(vp, hidden, vws, arrivals, dims->batch) : PackJob{};
   std::vector<CombineJob> merges;
@@ -750,7 +757,9 @@ int sd_verify_step_static(const sd_dims_t* dims, const void* q, const void* k_po
   st = check_kv(dims, kv_off, kv_len);
   if (st != SD_OK) return st;
   if (!(scale > 0.f) || !std::isfinite(scale)) return SD_ERR_INVALID_ARGUMENT;
-  if (step_ws(dims, kv_len, scale, hidden, nullptr) > SD_STATIC_SCRATCH_BYTES) return SD_ERR_WORKSPACE;
+  VocabPlan vp;
+  if (!step_plan(dims, step_attention_ws(dims, kv_len, scale, nullptr), hidden != nullptr, SD_STATIC_SCRATCH_BYTES, &vp))
+    return SD_ERR_WORKSPACE;
   void* ws = nullptr;
   st = static_scratch(&ws);
   if (st != SD_OK) return st;
@@ -761,8 +770,7 @@ int sd_verify_step_static(const sd_dims_t* dims, const void* q, const void* k_po
 
 const char* sd_vocab_kernel_name(const sd_dims_t* dims) {
   if (check_dims(dims) != SD_OK) return nullptr;
-  const VocabPlan p = vocab_plan(dims->dtype, dims->batch * (dims->gamma + 1), dims->hidden, dims->vocab,
-                                 (dims->flags & SD_FLAG_PACKED_VOCAB) != 0);
+  const VocabPlan p = logits_plan(dims);
   if (dims->dtype == SD_DTYPE_F32) return "vocab_f32_kernel";
   if (p.rows) return "vocab_bf16_deep_kernel";  // the row-major form
   if (!p.deep) return "vocab_bf16_kernel";

@@ -96,7 +96,7 @@ struct VocabPlan {
   bool lines;      // line schedule (float32, or bf16 with few rows)
   bool rows;       // row schedule (bf16, more rows, row-major W)
 };
-VocabPlan vocab_plan(int dtype, int M, int K, int V, bool packed);
+VocabPlan vocab_plan(int dtype, int M, int K, int V, bool packed, bool small = false);
 size_t vocab_packed_bytes(int K, int V);
 hipError_t launch_pack_vocab(int K, int V, const void* w, void* out, hipStream_t stream);
 // Workspace of launch_vocab: the per-(row, tile) softmax statistics
@@ -116,7 +116,7 @@ constexpr int kLineMaxBlocks = 4;  // 16-row blocks per workgroup of the line sc
 // The line schedule (lines.hip): a wave owns 16 vocabulary entries, a
 // workgroup p.mblocks 16-row blocks.  line_plan fills nbw, waves, mtiles and
 // mblocks for `blocks` 16-row blocks in all.
-void line_plan(int blocks, int V, VocabPlan* p);
+void line_plan(int blocks, int V, bool small, VocabPlan* p);
 hipError_t launch_vocab_lines(bool f32, const VocabPlan& p, const void* hidden, const void* w, float* logits,
                               float2* partials, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop,
                               int* clear, int nclear);

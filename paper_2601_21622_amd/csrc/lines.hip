@@ -233,11 +233,14 @@ void vocab_bf16_kernel(int M, int K, int V, int ntiles, int mtiles, const uint16
 // measured kernels: 32 x 5120 x 20000 takes 31 us with five waves (250
 // workgroups), 40 with eight (157); 52 x 6400 x 10687 47 with four, 51 with
 // three or two; 8 x 1504 x 115716 54 with eight, 60 with six.
+// `small`: not fewer than four, whose statistics (8 bytes per row and tile) are
+// the least workspace a caller may bring.
 constexpr int kLineMaxWaves = 8;
-int line_waves(int V, int mtiles, int mblocks) {
+constexpr int kLineSmallWaves = 4;
+int line_waves(int V, bool small, int mtiles, int mblocks) {
   int best = kLineMaxWaves;
   double least = 0.0;
-  for (int nw = kLineMaxWaves; nw >= 1; --nw) {
+  for (int nw = kLineMaxWaves; nw >= (small ? kLineSmallWaves : 1); --nw) {
     const double groups = (double)((V + 16 * nw - 1) / (16 * nw)) * mtiles;
     const double rows = 16.0 * mblocks;
     const double cost = std::ceil(groups / 256.0) * (16 * nw + rows + 16) + 1.5 * rows * groups / 256.0;
@@ -297,11 +300,11 @@ hipError_t line_waves_of(bool f32, const LineCall& a) {
 
 }  // namespace
 
-void line_plan(int blocks, int V, VocabPlan* p) {
+void line_plan(int blocks, int V, bool small, VocabPlan* p) {
   p->nbw = 1;
   p->mtiles = (blocks + kLineMaxBlocks - 1) / kLineMaxBlocks;
   p->mblocks = (blocks + p->mtiles - 1) / p->mtiles;
-  p->waves = line_waves(V, p->mtiles, p->mblocks);
+  p->waves = line_waves(V, small, p->mtiles, p->mblocks);
 }
 
 hipError_t launch_vocab_lines(bool f32, const VocabPlan& p, const void* hidden, const void* w, float* logits,

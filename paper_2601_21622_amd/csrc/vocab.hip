@@ -11,7 +11,7 @@
 // fragment-ordered copy sd_pack_vocab makes at weight-load time (1 KB
 // contiguous per fragment).  The hidden rows, shared by every workgroup and
 // L2-resident, are staged per K-chunk in LDS in fragment order and read by
-// all waves.  Three schedules:
+// all waves.  Four schedules:
 //   * line (float32, or at most 64 hidden rows): lines.hip.
 //   * deep (more rows), MFMA 32x32x16: the hidden rows are first repacked
 //     (pack_hidden_kernel) into 32-row fragments that LDS DMA moves 1 KB at a
@@ -22,6 +22,7 @@
 //   * wide (deep rows, large vocabularies): four waves with four blocks of
 //     32 vocabulary entries each, a 512-wide tile whose accumulators fill
 //     both register files; W and hidden both go to LDS by buffer DMA.
+//   * row (row-major W in the deep schedule's four-wave tiles): rows.hip.
 //     vocab_plan picks, among the deep shapes and the wide one, the one whose
 //     per-CU inflow (W misses plus hidden hits) is smallest.  Workgroups that
 //     share a vocabulary tile (several M-tiles) are dealt to the same XCD.
@@ -698,7 +699,7 @@ hipError_t launch_pack_vocab(int K, int V, const void* w, void* out, hipStream_t
   return hipGetLastError();
 }
 
-VocabPlan vocab_plan(int dtype, int M, int K, int V, bool packed) {
+VocabPlan vocab_plan(int dtype, int M, int K, int V, bool packed, bool small) {
   VocabPlan p;
   p.packed = packed;
   p.lines = false;
@@ -710,7 +711,7 @@ VocabPlan vocab_plan(int dtype, int M, int K, int V, bool packed) {
   if (dtype == 0 || blocks <= kLineMaxBlocks) {
     p.deep = false;
     p.lines = true;
-    line_plan(blocks, V, &p);
+    line_plan(blocks, V, small, &p);
   } else {
     // The deep shape the inflow model prices lowest (ties go to the
     // narrower tile).

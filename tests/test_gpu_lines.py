@@ -63,3 +63,32 @@ def test_line_schedule_within_rounding_bound(dtype, rows, K, V, packed):
     want = (mx + np.log(np.exp(got - mx).sum(axis=1, keepdims=True)))[:, 0]
     # exp and the tile sums in float32, the fold in float64, the result rounded to float32
     assert np.all(np.abs(lse.cpu().double().numpy() - want) <= 1e-5 * np.maximum(1.0, np.abs(want)))
+
+
+@pytest.mark.parametrize("dtype,rows,K,V", [("f32", (1, 5), 256, 1000), ("bf16", (3, 3), 352, 6025), ("f32", (20, 4), 64, 3000)])
+def test_line_schedule_in_the_smallest_workspace(dtype, rows, K, V):
+    """Statistics of 64-entry tiles are all the workspace that logits need:
+    finer tiles are taken only where the workspace holds theirs.  Both plans
+    stay within the rounding bound of the sums; less is refused."""
+    (B, G), M = rows, rows[0] * rows[1]
+    announce(f"smallest workspace dtype={dtype} M={M} K={K} V={V}")
+    g = torch.Generator().manual_seed(M + K + V)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    h, w = torch.randn(M, K, generator=g).to(dt), (torch.randn(V, K, generator=g) / K ** 0.5).to(dt)
+    dims = sd.Dims(B, G - 1, 1, 1, 64, K, V, sd.SD_DTYPE_F32 if dtype == "f32" else sd.SD_DTYPE_BF16, 0)
+    least = (8 * M * ((V + 63) // 64) + 255) // 256 * 256
+    hd, wd = h.cuda(), w.cuda()
+    logits = torch.full((M, V), float("nan"), device="cuda")
+    lse = torch.full((M,), float("nan"), device="cuda")
+    room = torch.full((least + 256,), 0xA5, dtype=torch.uint8, device="cuda")
+    sd.sd_verify_logits(dims, hd, wd, logits, lse, room[:least])
+    ref = h.double().numpy() @ w.double().numpy().T
+    bound = K * 2.0 ** -24 * (np.abs(h.double().numpy()) @ np.abs(w.double().numpy()).T) + 1e-30
+    got = logits.cpu().double().numpy()
+    assert np.all(np.abs(got - ref) <= bound)
+    mx = got.max(axis=1, keepdims=True)
+    want = (mx + np.log(np.exp(got - mx).sum(axis=1, keepdims=True)))[:, 0]
+    assert np.all(np.abs(lse.cpu().double().numpy() - want) <= 1e-5 * np.maximum(1.0, np.abs(want)))
+    assert bool((room[least:] == 0xA5).all())
+    with pytest.raises(sd.SdError):
+        sd.sd_verify_logits(dims, hd, wd, logits, lse, room[:least - 256])
