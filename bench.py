@@ -549,16 +549,17 @@ def main() -> int:
     # kernel its plan picks; attention runs the register-staged kernel for a
     # single 16-row block per KV head.
     vocab_kernel = sd.sd_vocab_kernel_name(dims)
+    vocab_source = "lines.hip" if vocab_kernel in ("vocab_bf16_kernel", "vocab_f32_kernel") else "vocab.hip"
     rows = G * (cfg.n_q_heads // cfg.n_kv_heads)
     attn_kernel = "attn_bf16_reg_kernel" if rows <= 16 else "attn_bf16_kernel"
     roof_attn = {"bound": "hbm", "achieved": attn_gbps, "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                  "frac": attn_gbps / HBM_PEAK_GBPS, "traffic": counter_traffic(attn_kernel, cfg.name, "attention.hip"),
                  "kernel": attn_kernel, "bytes_per_launch": attn_bytes, "ms_per_launch": float(st_mean[0])}
     roof_vocab = {"bound": "hbm", "achieved": vocab_gbps, "peak": HBM_PEAK_GBPS, "unit": "GB/s",
-                  "frac": vocab_gbps / HBM_PEAK_GBPS, "traffic": counter_traffic(vocab_kernel, cfg.name, "vocab.hip"),
+                  "frac": vocab_gbps / HBM_PEAK_GBPS, "traffic": counter_traffic(vocab_kernel, cfg.name, vocab_source),
                   "kernel": vocab_kernel, "bytes_per_launch": vocab_bytes, "ms_per_launch": float(st_mean[1]),
                   "mfma_frac": vocab_tflops / BF16_MFMA_PEAK_TFLOPS,
-                  "mfma_busy_counters": counter_mfma_busy(vocab_kernel, cfg.name, "vocab.hip")}
+                  "mfma_busy_counters": counter_mfma_busy(vocab_kernel, cfg.name, vocab_source)}
     dominant = "vocab" if st_mean[1] >= st_mean[0] else "attention"
     roof = roof_vocab if dominant == "vocab" else roof_attn
 
