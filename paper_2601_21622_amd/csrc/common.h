@@ -218,8 +218,10 @@ __device__ __forceinline__ float key_value(uint32_t k) {
 // exp(t) for t <= 0, to about an ulp: 2^(t log2 e) on the hardware exponential,
 // with the product's rounding error (and log2 e's) put back to first order.
 // Half the instructions of expf, whose range checks t <= 0 does not need; the
-// pass over a row is bound by them.
+// pass over a row is bound by them.  Masked entries (-inf, the lowest float) come
+// as -200, whose exponential is 0 too: their products would overflow to NaN.
 __device__ __forceinline__ float exp_neg(float t) {
+  t = fmaxf(t, -200.f);
   const float h = t * kLog2e;
   const float l = fmaf(t, 1.925963033500e-8f, fmaf(t, kLog2e, -h));  // log2 e = kLog2e + 1.92596e-8
   const float e = __builtin_amdgcn_exp2f(h);

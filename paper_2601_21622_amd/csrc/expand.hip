@@ -109,7 +109,8 @@ void expand_kernel(ExpandArgs e, const float* __restrict__ logits, int32_t* __re
 #pragma unroll
     for (int u = 0; u < kExpUnroll; ++u) {
       const bool in = base + u * kExpThreads + lane < e.V && xs[u] != -INFINITY;
-      acc += in ? (double)exp_neg(xs[u] - m) : 0.0;
+      const float t = xs[u] - m;
+      acc += in ? (double)(t != t ? t : exp_neg(t)) : 0.0;
     }
   }
   if (lane < kExpandMaxK) s_lst[wave][lane] = lane < e.k ? lst : 0;

@@ -418,7 +418,8 @@ void warp_kernel(int V, const float* __restrict__ logits, float inv_t, int greed
     }
     __syncthreads();
     // As values (-0 equal to +0: a tile maximum may be either); a superset.
-    const float bound = key_value(s_bound);
+    // With fewer threads that hold an entry than top_k (short rows): every entry.
+    const float bound = s_bound < order_key(-INFINITY) ? -INFINITY : key_value(s_bound);
     auto take = [&](int v, float xv) {
       if (xv >= bound) {
         const uint32_t i = atomicAdd(&s_n, 1u);

@@ -211,3 +211,26 @@ def test_sampled_accept_is_deterministic():
         outs.append([to_np(t) for t in (lse, mn, acc, tok)])
     for a, b in zip(*outs):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("V", [100, 1003, 40000])
+@pytest.mark.parametrize("T,k,p", [(1.0, 0, 1.0), (0.7, 0, 0.9), (1.0, 40, 1.0), (0.8, 40, 0.9), (1.0, 70, 0.95)])
+def test_masked_logits_carry_no_mass(V, T, k, p):
+    """Tokens masked by -inf or by the lowest float have no probability: cut
+    and log-sum-exp as the oracle's, also on rows with fewer 16-byte pieces than
+    top_k."""
+    announce(f"masked logits V={V} T={T} k={k} p={p}")
+    rng = np.random.default_rng(V + k)
+    B, G = 2, 3
+    x = (rng.standard_normal((B * G, V)) * 2.0).astype(np.float32)
+    x[0::3, rng.choice(V, V // 5, replace=False)] = -np.inf
+    x[1::3, rng.choice(V, V // 5, replace=False)] = np.finfo(np.float32).min
+    dims = sd.Dims.of(get_config("tiny").replace(batch=B, gamma=G - 1, vocab=V))
+    f = lambda *s, dt=torch.float32: torch.full(s, -7, dtype=dt, device="cuda")  # noqa: E731
+    lse, mn = f(B * G), f(B * G)
+    sd.sd_accept_resample_sampled(dims, sd.Sampling(T, k, p), torch.from_numpy(x).cuda(),
+                                  torch.full((B, G - 1, V), 1.0 / V, device="cuda"), f(B, G - 1, dt=torch.int32).zero_(),
+                                  f(B, G).fill_(0.5), np.full(B, 100, np.int32), lse, mn, f(B, dt=torch.int32),
+                                  f(B, G, dt=torch.int32), f(B, dt=torch.int32),
+                                  torch.empty(sd.sd_workspace_bytes(dims, 100), dtype=torch.uint8, device="cuda"))
+    _check_cut(x, T, k, p, to_np(lse), to_np(mn))
