@@ -20,8 +20,8 @@
 //     order, giving lse; q(child) = exp(logit - lse) with the difference kept
 //     exact, the logit taken from its key.
 // A row is one workgroup's, so a CU's inflow bounds it (128 KB take about 5
-// us); a second pass for the sums took as long again: 8 rows of 32,000 entries
-// 11.4 us against 20.4.
+// us); a second pass for the sums took as long again: a depth-5 tree of 8 rows of
+// 32,000 entries a launch or more takes 61 us against 101.
 // Children of node f are numbered first_child + f*k + j in rank order.
 #include <hip/hip_ext.h>
 
