@@ -107,13 +107,15 @@ constexpr int kLineBytes = 128;
 // DMA of one 1 KB block: lane l copies 16 bytes from g into LDS bytes lds +
 // 16l .. +15 (lds wave-uniform).  From inline assembly, so that the compiler
 // inserts no waits of its own between it and reads of other stages; the
-// kernel's vmcnt waits order it.  It sets M0 itself.
+// kernel's vmcnt waits order it.  It sets M0 itself, and waits the one state
+// that a load into LDS needs after that (the compiler's hazard pass does not
+// see into the string).
 template <bool NT>
 __device__ __forceinline__ void line_dma(const char* g, uint32_t lds) {
   if (NT)
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off nt" : : "s"(lds), "v"(g) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" : : "s"(lds), "v"(g) : "m0", "memory");
   else
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds), "v"(g) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds), "v"(g) : "m0", "memory");
 }
 
 // Fixed-order combination of the NW per-wave values of row r.
