@@ -337,17 +337,17 @@ struct TileLane {
 // LDS bytes lds + 16l .. +15.  gbase and lds are wave-uniform (scalar
 // registers).  Issued from inline assembly, so the compiler neither tracks it
 // nor inserts waits for it: the kernel's own vmcnt waits order it against the
-// LDS reads.  It sets M0 itself and waits the one state that a load into LDS
-// needs after that (the compiler's hazard pass does not see into the string).
-// The load carries the nontemporal hint (every row is read once).
+// LDS reads.  The load carries the nontemporal hint (every row is read once).
 // Both scalars pass through readfirstlane (free when the compiler already
 // holds them in scalar registers), since the instruction takes them only
-// from scalar registers.
+// from scalar registers.  The compiler's hazard pass does not see into the
+// string, so it waits for itself: five states after a readfirstlane that wrote
+// the base (s_mov and s_nop 3), which covers the one after M0's write.
 __device__ __forceinline__ void dma_block(uint32_t lds, const void* gbase, uint32_t voff) {
   const uint64_t g = (uint64_t)(uintptr_t)gbase;
   const uint64_t gu = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(g >> 32)) << 32) |
                       (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)g);
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %2 nt"
                :
                : "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(voff), "s"((const void*)(uintptr_t)gu)
                : "m0", "memory");
