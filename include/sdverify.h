@@ -202,6 +202,9 @@ SD_API int sd_accept_resample(const sd_dims_t* dims, const float* logits_or_prob
  * [M][n_q_heads * head_dim], which then must equal dims->hidden), then
  * sd_accept_resample on the logits and row_lse it produced.  Arguments as in
  * the three calls; attn_out, logits, row_lse are outputs the caller owns.
+ * `hidden` is read before attn_out is written: where it lies in attn_out the
+ * projection takes what the buffer held before the call (pass NULL for this
+ * step's attention output).  The paged, static and tree steps do the same.
  *   kernel_events  (host) NULL, or 6 hipEvent_t handles (created with timing
  *                  enabled): start/stop of the attention kernel (without its
  *                  combine), of the vocabulary projection kernel (for more
@@ -296,7 +299,9 @@ SD_API int sd_accept_resample_sampled(const sd_dims_t* dims, const sd_sampling_t
  * sd_verify_step with a warped target: attention, projection, then
  * sd_accept_resample_sampled on the logits it produced.  Arguments as in
  * sd_verify_step and sd_accept_resample_sampled; kernel_events' last pair
- * spans the warp kernel through the pick kernel.
+ * spans the warp kernel through the pick kernel.  Here attn_out is written
+ * before `hidden` is read where the two overlap: hidden == attn_out projects
+ * this step's attention output, as NULL does.
  */
 SD_API int sd_verify_step_sampled(const sd_dims_t* dims, const sd_sampling_t* sampling, const void* q,
                                   const void* k_pool, const void* v_pool, const int64_t* kv_off,

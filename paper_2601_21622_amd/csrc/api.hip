@@ -33,6 +33,11 @@ constexpr int64_t kMaxKvLen = int64_t(1) << 30;
 
 bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 
+bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return x < y + nb && y < x + na;
+}
+
 size_t elem_size(int dtype) { return dtype == SD_DTYPE_BF16 ? 2 : 4; }
 
 size_t align_up(size_t x) { return (x + 255) & ~size_t(255); }
@@ -565,11 +570,14 @@ int sd_verify_step_sampled(const sd_dims_t* dims, const sd_sampling_t* sampling,
   if (st != SD_OK) return st;
   // As in the chain step the attention merge rides in the acceptance launch,
   // its partials in a region of their own; a workspace that only holds the
-  // stages one after another gets the merge as a launch of its own.
+  // stages one after another gets the merge as a launch of its own, and so do
+  // hidden rows that lie in attn_out, which are this step's attention output.
   const size_t attn_bytes = step_attention_ws(dims, kv_len, scale, nullptr);
   VocabPlan vp;
   if (!step_plan(dims, attn_bytes, false, workspace_bytes, &vp)) return SD_ERR_WORKSPACE;
-  const bool defer = hidden != nullptr && workspace_bytes >= step_ws(dims, vp, attn_bytes, true);
+  const size_t es = elem_size(dims->dtype), M = static_cast<size_t>(dims->batch) * (dims->gamma + 1);
+  const bool defer = hidden != nullptr && workspace_bytes >= step_ws(dims, vp, attn_bytes, true) &&
+                     !overlap(hidden, M * dims->hidden * es, attn_out, M * dims->n_q_heads * dims->head_dim * es);
 
   hipEvent_t ev[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
   if (kernel_events != nullptr)

@@ -135,6 +135,33 @@ def test_sampled_accept_matches_oracle(shape, setting):
     assert agree >= 0.9
 
 
+@pytest.mark.parametrize("rows,shift", [((3, 4), 0), ((3, 4), 1), ((16, 5), 0), ((16, 5), 3)])
+def test_sampled_step_on_hidden_rows_inside_attn_out(rows, shift):
+    """Hidden rows that lie in attn_out, wholly or from row `shift` on, are the
+    step's own attention output (line schedule, and the packed one, whose hidden
+    rows are repacked first): logits as the separate calls give them."""
+    B, G = rows
+    cfg = get_config("vicuna7b").replace(batch=B, gamma=G - 1, n_q_heads=4, n_kv_heads=4, hidden=512, vocab=3001,
+                                         lengths=("explicit", tuple(300 + 40 * i for i in range(B))))
+    announce(f"sampled step, hidden in attn_out B={B} G={G} shift={shift}")
+    x = make_inputs(cfg)
+    db = DeviceBatch(x, packed_vocab=True)
+    M = B * G
+    room = torch.zeros((M + shift, 512), dtype=torch.bfloat16, device="cuda").normal_()
+    hidden, attn = room[shift:], room[:M].view(B, G, 4, 128)
+    db.attention()
+    room_ref = room.clone()
+    room_ref[:M] = db.attn.view(M, 512)
+    db.logits_(room_ref[shift:].contiguous())
+    want = db.logits.clone()
+    mn = torch.empty_like(db.lse)
+    sd.sd_verify_step_sampled(db.dims, sd.Sampling(1.0, 0, 0.9), db.q, db.k, db.v, x.kv_off, x.kv_len, db.scale,
+                              hidden, db.w, db.q_draft, db.draft, db.u, attn, db.logits, db.lse, mn,
+                              db.accept_len, db.out_tok, db.new_kv_len, db.ws)
+    assert torch.equal(room, room_ref)
+    assert torch.equal(db.logits, want)
+
+
 def test_sampled_step_matches_oracle():
     cfg = get_config("vicuna7b").replace(batch=3, n_q_heads=4, n_kv_heads=4, hidden=512, vocab=3001,
                                          lengths=("explicit", (6, 300, 1100)))
