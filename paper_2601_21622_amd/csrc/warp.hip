@@ -125,49 +125,29 @@ __device__ __forceinline__ unsigned long long entry_key(uint32_t k, int v) {
 }
 
 // Calls f(v, x[v]) for every element of the row, this thread's share, with
-// several loads in flight per thread (4 x float4 when the row is 16-byte
-// aligned, else 8 scalars).  The order in which a thread sees its elements is
-// unspecified; every reduction built on it is order-independent.
+// four 16-byte loads in flight (rows need only their entries' alignment); the
+// last V % 4 entries are single loads.  Which entries a thread sees, and in
+// which order, depends on V alone, so a float64 sum over them does not depend
+// on where the row lies.
 template <typename F>
 __device__ __forceinline__ void row_pass(const float* __restrict__ x, int V, F&& f) {
+  constexpr int U = 4;
   const int tid = threadIdx.x;
-  if ((V & 3) == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0) {
-    constexpr int U = 4;
-    const float4* x4 = reinterpret_cast<const float4*>(x);
-    const int V4 = V >> 2;
-    int i = tid;
-    for (; i + (U - 1) * kWarpThreads < V4; i += U * kWarpThreads) {
-      float4 r[U];
+  const int V4 = V >> 2;
+  auto quad = [&](int i, const f32x4& r) {
 #pragma unroll
-      for (int u = 0; u < U; ++u) r[u] = x4[i + u * kWarpThreads];
+    for (int e = 0; e < 4; ++e) f(4 * i + e, r[e]);
+  };
+  int i = tid;
+  for (; i + (U - 1) * kWarpThreads < V4; i += U * kWarpThreads) {
+    f32x4 r[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int v = 4 * (i + u * kWarpThreads);
-        f(v, r[u].x);
-        f(v + 1, r[u].y);
-        f(v + 2, r[u].z);
-        f(v + 3, r[u].w);
-      }
-    }
-    for (; i < V4; i += kWarpThreads) {
-      const float4 r = x4[i];
-      f(4 * i, r.x);
-      f(4 * i + 1, r.y);
-      f(4 * i + 2, r.z);
-      f(4 * i + 3, r.w);
-    }
-  } else {
-    constexpr int U = 8;
-    int v = tid;
-    for (; v + (U - 1) * kWarpThreads < V; v += U * kWarpThreads) {
-      float r[U];
+    for (int u = 0; u < U; ++u) r[u] = *reinterpret_cast<const f32x4_u*>(x + 4 * (i + u * kWarpThreads));
 #pragma unroll
-      for (int u = 0; u < U; ++u) r[u] = x[v + u * kWarpThreads];
-#pragma unroll
-      for (int u = 0; u < U; ++u) f(v + u * kWarpThreads, r[u]);
-    }
-    for (; v < V; v += kWarpThreads) f(v, x[v]);
+    for (int u = 0; u < U; ++u) quad(i + u * kWarpThreads, r[u]);
   }
+  for (; i < V4; i += kWarpThreads) quad(i, *reinterpret_cast<const f32x4_u*>(x + 4 * i));
+  if (tid < (V & 3)) f(4 * V4 + tid, x[4 * V4 + tid]);
 }
 
 struct Level {
