@@ -311,14 +311,23 @@ void warp_kernel(int V, const float* __restrict__ logits, float inv_t, int greed
       }
     }
   };
-  const bool by_tiles = tiles != nullptr && (greedy || top_k == 0 || top_k >= V || top_k > kWave || top_k <= ntiles);
+  bool by_tiles = tiles != nullptr && (greedy || top_k == 0 || top_k >= V || top_k > kWave || top_k <= ntiles);
   uint32_t bk = 0;
   int bi = 0x7fffffff;
+  bool odd = false;  // a tile's sum is no number: NaN or infinite logits, whose order the row itself gives
   if (by_tiles) {
-    for (int t = tid; t < ntiles; t += kWarpThreads) merge(bk, bi, order_key(tiles[t].x), t);
-  } else {
-    row_pass(x, V, [&](int v, float xv) { merge(bk, bi, order_key(xv), v); });
+    for (int t = tid; t < ntiles; t += kWarpThreads) {
+      const float2 st = tiles[t];
+      merge(bk, bi, order_key(st.x), t);
+      odd |= st.y != st.y;
+    }
+    if (__syncthreads_or(odd)) {
+      by_tiles = false;
+      bk = 0;
+      bi = 0x7fffffff;
+    }
   }
+  if (!by_tiles) row_pass(x, V, [&](int v, float xv) { merge(bk, bi, order_key(xv), v); });
   // This thread's best entry (or tile): a lower bound of one entry of the row.
   const unsigned long long tkey = bi == 0x7fffffff ? 0ull : entry_key(bk, bi);
   // The threads' smallest, without the thread that holds a partial last tile.
@@ -397,11 +406,12 @@ void warp_kernel(int V, const float* __restrict__ logits, float inv_t, int greed
       }
     }
     __syncthreads();
-    // As values (-0 equal to +0: a tile maximum may be either); a superset.
-    // With fewer threads that hold an entry than top_k (short rows): every entry.
+    // As values (-0 equal to +0: a tile maximum may be either); a superset,
+    // with every NaN (they rank by their keys).  With fewer threads that hold
+    // an entry than top_k (short rows): every entry.
     const float bound = s_bound < order_key(-INFINITY) ? -INFINITY : key_value(s_bound);
     auto take = [&](int v, float xv) {
-      if (xv >= bound) {
+      if (!(xv < bound)) {
         const uint32_t i = atomicAdd(&s_n, 1u);
         if (i < (uint32_t)kCand) s_cand[i] = entry_key(order_key(xv), v);
       }

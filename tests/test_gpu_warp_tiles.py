@@ -69,3 +69,42 @@ def test_step_warp_equals_standalone(shape, T, k, p):
         assert np.array_equal(to_np(a), to_np(b))
     if scale >= 0.3 and not ties:
         _check_cut(to_np(logits)[:2], T, k, p, to_np(got[0])[:2], to_np(got[1])[:2])
+
+
+@pytest.mark.parametrize("T,k,p", [(0.0, 0, 1.0), (0.7, 0, 1.0), (1.0, 0, 0.9), (0.8, 40, 0.9), (0.6, 200, 0.95)])
+@pytest.mark.parametrize("V,bad,f32", [(3000, float("nan"), True), (128256, float("nan"), True),
+                                       (3000, float("nan"), False), (3000, float("inf"), False)])
+def test_step_warp_with_logits_that_are_no_numbers(V, bad, f32, T, k, p):
+    """A weight row of NaN (positive ones with float32, negative ones with
+    bfloat16) gives every row of logits an entry that tile maxima do not see.
+    The step falls back on the row itself, where such entries rank by their
+    keys: normaliser, cut and tokens as the standalone call gives them on the
+    step's logits; a positive NaN or an infinity leaves no finite normaliser."""
+    announce(f"warp tiles, no numbers V={V} bad={bad} f32={f32} T={T} k={k} p={p}")
+    dt = torch.float32 if f32 else torch.bfloat16
+    B, G, K, D, L = 2, 3, 64, 64, 8
+    M = B * G
+    g = torch.Generator().manual_seed(V + k)
+    h = torch.rand(M, K, generator=g).to(dt).cuda()
+    w = torch.randn(V, K, generator=g) * 0.4
+    w[V // 3] = bad
+    w = w.to(dt).cuda()
+    dims = sd.Dims(B, G - 1, 1, 1, D, K, V, sd.SD_DTYPE_F32 if f32 else sd.SD_DTYPE_BF16, 0)
+    kv_len, kv_off = np.full(B, L, np.int32), np.arange(B, dtype=np.int64) * L * D
+    kv = torch.randn(B * L * D, generator=g).to(dt).cuda()
+    q = torch.randn(B, G, 1, D, generator=g).to(dt).cuda()
+    qd = torch.softmax(torch.randn(B, G - 1, V, generator=g), 2).cuda()
+    draft = torch.randint(0, V, (B, G - 1), generator=g).int().cuda()
+    u = torch.rand(B, G, generator=g).cuda()
+    ws = torch.zeros(sd.sd_workspace_bytes(dims, L), dtype=torch.uint8, device="cuda")
+    f = lambda *s, dt=torch.float32: torch.full(s, -7, dtype=dt, device="cuda")  # noqa: E731
+    outs = [(f(M), f(M), f(B, dt=torch.int32), f(B, G, dt=torch.int32), f(B, dt=torch.int32)) for _ in range(2)]
+    attn, logits = torch.empty_like(q), torch.empty(M, V, device="cuda")
+    sd.sd_verify_step_sampled(dims, sd.Sampling(T, k, p), q, kv, kv, kv_off, kv_len, 0.125, h, w, qd, draft, u, attn,
+                              logits, *outs[0], ws)
+    assert not bool(torch.isfinite(logits[:, V // 3]).any())
+    sd.sd_accept_resample_sampled(dims, sd.Sampling(T, k, p), logits, qd, draft, u, kv_len, *outs[1], ws)
+    for a, b in zip(*outs):
+        assert np.array_equal(to_np(a), to_np(b), equal_nan=True)
+    if T > 0 and (f32 or np.isinf(bad)):
+        assert not np.isfinite(to_np(outs[0][0])).any()
