@@ -266,7 +266,8 @@ SD_API int sd_verify_step_static(const sd_dims_t* dims, const void* q, const voi
  * the argmax of row l + 1; u and q do not change the result.
  * "Order" is the order of float32 values with -0 below +0.  Logits must be
  * finite.  Masses are evaluated in float32 and summed as 64-bit fixed point
- * (2^(62 - ceil(log2 V)) per unit), so the cut is deterministic; it may differ
+ * (2^(62 - ceil(log2 V)) per unit), a whole row's (no top_k) in float64 in an
+ * order that depends on V alone, so the cut is deterministic; it may differ
  * from a float64 evaluation only when top_p lies within about 1e-6 of a
  * cumulative mass.
  */

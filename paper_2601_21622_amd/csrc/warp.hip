@@ -14,19 +14,22 @@
 //      pass, or in a step from the projection's tile maxima (greedy then reads
 //      only the tiles that reach it);
 //   2. a pass that keeps the few thousand largest entries in LDS and, with no
-//      top-k cut, sums the row's mass; with a top-k cut and tile maxima only
+//      top-k cut, sums the row's mass; for top-k up to 64 with tile maxima only
 //      tiles that reach the bound are read;
 //   3. the cut among the kept entries: a wave sort for top-k up to 64, else a
 //      radix descent on counts (top-k) or masses against ceil(top_p * kept
-//      mass).  Rows whose cut lies elsewhere (flat or tied rows) take more
-//      passes: a histogram of the row's mass and the entries of one of its
-//      bins, or a radix descent over the row's 32-bit order keys, 11, 11 and 10
-//      bits per level;
+//      mass).  Rows whose cut lies elsewhere take more passes: flat or tied
+//      rows a histogram of the row's mass and the entries of one of its bins,
+//      and what is left (large top-k) a radix descent over the row's 32-bit
+//      order keys, 11, 11 and 10 bits per level;
 //   4. lse = max / T + log(kept mass).
 // A pass over 128,256 entries by one workgroup is bound by its instructions (64
 // lanes a cycle), so a pass does little per entry: float64 sums per thread
 // instead of fixed-point ones, no vote across the wave.  224 rows of 128,256,
 // top-p 0.9 in a step: 106 us with three passes of LDS atomics, 40-48 with one.
+// Rows off that shape, 224 of 128,256 with the acceptance: within a nat of each
+// other 126 -> 96 us, 17 distinct values 203 -> 147, all equal 702 -> 172 (the
+// radix descent's atomics meet in few buckets).
 // In the radix descent over a long row the second level also gathers the keys
 // inside the first level's bucket into LDS; when they fit, the third level
 // reads those instead of the row (the same entries, so the same integer
@@ -57,6 +60,8 @@ constexpr int kCand = 2048;  // candidates the small-k path can hold
 // instead of passing over the row again (when they fit).
 constexpr int kKeep = 16384;
 constexpr int kKeepMinV = 65536;
+// Key of the lowest float: entries down here are masked.
+constexpr uint32_t kMaskedKey = 0x00800000u;
 // Largest entries that each thread keeps in LDS (the same space).
 constexpr int kKeepEach = 24;
 static_assert(kKeepEach * kWarpThreads >= kKeep, "one array serves both");
@@ -208,15 +213,22 @@ __device__ void select_bucket(const uint32_t* hcnt, const unsigned long long* hm
   }
 }
 
+// Kinds of cut, a kernel each, with tile maxima (TILES) or without: one kernel
+// for all took 77 KB of instructions, more than the CU's cache holds.
+enum Cut { kGreedy, kSmallK, kLargeK, kNoK };
+
+template <int CUT, bool TILES>
 __global__ __launch_bounds__(kWarpThreads)
-void warp_kernel(int V, const float* __restrict__ logits, float inv_t, int greedy, int top_k, float top_p,
-                 int scale, const float2* __restrict__ partials, int ntiles, int tile_n, WarpRow* __restrict__ out, float* __restrict__ row_lse,
-                 float* __restrict__ row_min_logit) {
+void warp_kernel(int V, const float* __restrict__ logits, float inv_t, int top_k, float top_p, int scale,
+                 const float2* __restrict__ partials, int ntiles, int tile_n, WarpRow* __restrict__ out,
+                 float* __restrict__ row_lse, float* __restrict__ row_min_logit) {
+  constexpr bool greedy = CUT == kGreedy;
+  constexpr bool cut_k = CUT == kSmallK || CUT == kLargeK;
   __shared__ uint32_t hcnt[kBuckets];
   __shared__ unsigned long long hmass[kBuckets];
   __shared__ uint32_t w_key[kWarpWaves];
   __shared__ int w_idx[kWarpWaves];
-  __shared__ uint32_t w_low[kWarpWaves], s_low;
+  __shared__ uint32_t w_low[kWarpWaves];
   __shared__ unsigned long long w_sum[kWarpWaves];
   __shared__ double w_mass[kWarpWaves];
   __shared__ uint32_t s_kmax, s_bucket, s_cnt_above;
@@ -288,7 +300,7 @@ void warp_kernel(int V, const float* __restrict__ logits, float inv_t, int greed
   };
   // With the projection's tile statistics, from the tile maxima: only greedy
   // needs the entry itself, and then reads the tiles that reach the maximum.
-  const float2* tiles = partials != nullptr ? partials + (int64_t)row * ntiles : nullptr;
+  const float2* tiles = partials + (TILES ? (int64_t)row * ntiles : 0);
   // f(v, x[v]) for every entry of the tiles whose maximum reaches `bound`
   // (tiles w, w + 16, ... on wave w).
   auto tile_pass = [&](float bound, auto&& f) {
@@ -311,7 +323,7 @@ void warp_kernel(int V, const float* __restrict__ logits, float inv_t, int greed
       }
     }
   };
-  bool by_tiles = tiles != nullptr && (greedy || top_k == 0 || top_k >= V || top_k > kWave || top_k <= ntiles);
+  bool by_tiles = TILES && (CUT != kSmallK || top_k <= ntiles);
   uint32_t bk = 0;
   int bi = 0x7fffffff;
   bool odd = false;  // a tile's sum is no number: NaN or infinite logits, whose order the row itself gives
@@ -330,13 +342,7 @@ void warp_kernel(int V, const float* __restrict__ logits, float inv_t, int greed
   if (!by_tiles) row_pass(x, V, [&](int v, float xv) { merge(bk, bi, order_key(xv), v); });
   // This thread's best entry (or tile): a lower bound of one entry of the row.
   const unsigned long long tkey = bi == 0x7fffffff ? 0ull : entry_key(bk, bi);
-  // The threads' smallest, without the thread that holds a partial last tile.
-  const bool part = by_tiles && ntiles > 1 && V % tile_n != 0 && tid == (ntiles - 1) % kWarpThreads;
-  uint32_t low = bi == 0x7fffffff || part ? 0xffffffffu : bk;
-  for (int off = 32; off >= 1; off >>= 1) {
-    merge(bk, bi, __shfl_xor(bk, off), __shfl_xor(bi, off));
-    low = min(low, (uint32_t)__shfl_xor((int)low, off));
-  }
+  for (int off = 32; off >= 1; off >>= 1) merge(bk, bi, __shfl_xor(bk, off), __shfl_xor(bi, off));
   if (greedy && by_tiles) {
     __shared__ float s_top;
     if (lane == 0) w_key[wave] = bk;
@@ -357,20 +363,14 @@ void warp_kernel(int V, const float* __restrict__ logits, float inv_t, int greed
   if (lane == 0) {
     w_key[wave] = bk;
     w_idx[wave] = bi;
-    w_low[wave] = low;
   }
   __syncthreads();
   if (tid == 0) {
     uint32_t k = w_key[0];
     int i = w_idx[0];
-    uint32_t lo = w_low[0];
-    for (int w = 1; w < kWarpWaves; ++w) {
-      merge(k, i, w_key[w], w_idx[w]);
-      lo = min(lo, w_low[w]);
-    }
+    for (int w = 1; w < kWarpWaves; ++w) merge(k, i, w_key[w], w_idx[w]);
     s_kmax = k;
     s_amax = i;
-    s_low = lo;
   }
   __syncthreads();
   const int amax = s_amax;
@@ -389,7 +389,8 @@ void warp_kernel(int V, const float* __restrict__ logits, float inv_t, int greed
   uint32_t theta = 0;
   unsigned long long W = 0;
   bool have_k = false, have_p = false;
-  if (top_k >= 1 && top_k <= kWave && top_k < V) {
+  bool few = false;  // fewer unmasked entries than a small top_k
+  if (CUT == kSmallK) {
     // Small k: the k-th largest of the threads' best entries bounds the k-th
     // largest logit from below (k threads reach it), so the entries at or
     // above it hold the top-k set and all its ties.  They are collected in
@@ -408,19 +409,25 @@ void warp_kernel(int V, const float* __restrict__ logits, float inv_t, int greed
     __syncthreads();
     // As values (-0 equal to +0: a tile maximum may be either); a superset,
     // with every NaN (they rank by their keys).  With fewer threads that hold
-    // an entry than top_k (short rows): every entry.
-    const float bound = s_bound < order_key(-INFINITY) ? -INFINITY : key_value(s_bound);
+    // an unmasked entry than top_k (short rows, or nearly all masked): every
+    // unmasked entry.
+    const float bound = s_bound <= kMaskedKey ? key_value(kMaskedKey + 1) : key_value(s_bound);
     auto take = [&](int v, float xv) {
       if (!(xv < bound)) {
         const uint32_t i = atomicAdd(&s_n, 1u);
         if (i < (uint32_t)kCand) s_cand[i] = entry_key(order_key(xv), v);
       }
     };
-    if (by_tiles) tile_pass(bound, take);
+    // A wave's tiles come one after another: only on rows of several rounds of
+    // loads (20 rows of 5003, 16-wide tiles: 38 us a step by tiles, 36 without).
+    if (by_tiles && V > kWarpThreads * 16) tile_pass(bound, take);
     else row_pass(x, V, take);
     __syncthreads();
     const uint32_t n = s_n;
-    if (n <= (uint32_t)kCand) {  // otherwise (masses of ties at the bound) the radix descent below
+    few = n < (uint32_t)top_k;
+    // Otherwise (masses of ties at the bound, or masked entries in the set) the
+    // radix descent below.
+    if (!few && n <= (uint32_t)kCand) {
       if (wave == 0) {
         unsigned long long lst = 0;
         for (uint32_t base = 0; base < n; base += kWave)
@@ -479,20 +486,41 @@ void warp_kernel(int V, const float* __restrict__ logits, float inv_t, int greed
   // pass, per thread in float64).  The bound is the smallest tile maximum where
   // that leaves top_k entries, else 0.15 of the tile maxima's spread below it
   // (3 to 10 % of a normal row), or without tiles a tenth of the spread above the
-  // smallest of the threads' maxima (3 % of a 128,256-entry normal row); a
-  // bound that keeps too many or too few only costs time, the cut is then
-  // found from the whole row.
-  const bool cut_k = top_k >= 1 && top_k < V;
+  // smallest of the threads' maxima (3 % of a 128,256-entry normal row, half of
+  // a 1000-entry one); a bound that keeps too many or too few only costs time,
+  // the cut is then found from the whole row.  Not tried where it would only
+  // cost that time: with more top_k than maxima that it goes by (eight per
+  // tile: those of normal rows lie that dense; 40 rows of 32,000, top-k 5000:
+  // 50 us tried, 44 not) unless all unmasked entries of a short row fit, and for
+  // top_p in rows whose entries lie within a nat, where the largest few hold
+  // too little (0.05 normal, top-p 0.95: 49 us, 40).
   bool among = false;  // the cut is among the kept entries
   int mine = 0;        // this thread's, at s_keep[i * kWarpThreads + tid]
   uint32_t kbase = 0;  // a key no kept entry is below
   uint32_t kmax = m == 0.f ? order_key(0.f) : s_kmax;  // and one none is above
   double mass = 0.0;   // of the row, this thread's share
   const bool whole = !have_k && !cut_k;
-  if (!have_k && (cut_k || top_p < 1.f)) {
-    const float lowest = key_value(s_low);
-    const float bound = !by_tiles ? lowest + 0.1f * (m - lowest)
-                                  : (cut_k && top_k <= ntiles ? lowest : lowest - 0.15f * (m - lowest));
+  float lowest = m;    // the smallest of the threads' (or tiles') unmasked maxima
+  const bool few_k = top_k <= (by_tiles ? 8 * ntiles : min(V / 4, kWarpThreads));
+  const bool near_k = cut_k && !few && (few_k || V <= 4 * kWarpThreads);
+  if (!have_k && (cut_k ? near_k : top_p < 1.f)) {
+    // Without the thread that holds a partial last tile.
+    const bool part = by_tiles && ntiles > 1 && V % tile_n != 0 && tid == (ntiles - 1) % kWarpThreads;
+    const uint32_t own = (uint32_t)(tkey >> 32);
+    uint32_t low = own <= kMaskedKey || part ? 0xffffffffu : own;
+    for (int off = 32; off >= 1; off >>= 1) low = min(low, (uint32_t)__shfl_xor((int)low, off));
+    if (lane == 0) w_low[wave] = low;
+    __syncthreads();
+    for (int w = 0; w < kWarpWaves; ++w) low = min(low, w_low[w]);
+    if (low != 0xffffffffu) lowest = key_value(low);
+  }
+  const float spread = (m - lowest) * inv_t;
+  const bool flat = whole && top_p < 1.f && spread < 1.f && V > 4 * kWarpThreads;
+  const bool gather = !have_k && (near_k || (whole && top_p < 1.f && !flat));
+  if (gather) {
+    const float bound = cut_k && !few_k ? key_value(kMaskedKey + 1)
+                        : !by_tiles     ? lowest + 0.1f * (m - lowest)
+                                        : (cut_k && top_k <= ntiles ? lowest : lowest - 0.15f * (m - lowest));
     kbase = order_key(bound == 0.f ? -0.f : bound);  // -0 passes as +0 does
     for (int i = tid; i < kBuckets; i += kWarpThreads) hmass[i] = 0;
     auto take = [&](int, float xv) {
@@ -506,10 +534,8 @@ void warp_kernel(int V, const float* __restrict__ logits, float inv_t, int greed
         mass += (double)exp_neg((xv - m) * inv_t);
         take(v, xv);
       });
-    else if (by_tiles)
-      tile_pass(bound, take);
     else
-      row_pass(x, V, take);
+      row_pass(x, V, take);  // nearly every tile reaches the bound
     // Kept values to keys; their count, or their mass.
     unsigned long long near = cut_k ? (unsigned long long)mine : 0ull;
     for (int i = 0; i < min(mine, kKeepEach); ++i) {
@@ -523,7 +549,7 @@ void warp_kernel(int V, const float* __restrict__ logits, float inv_t, int greed
       w_sum[wave] = near;
       w_key[wave] = over;
     }
-  } else if (whole) {
+  } else if (whole && !flat) {
     row_pass(x, V, [&](int, float xv) { mass += (double)exp_neg((xv - m) * inv_t); });
   }
   if (whole) {
@@ -536,7 +562,7 @@ void warp_kernel(int V, const float* __restrict__ logits, float inv_t, int greed
     for (int w = 0; w < kWarpWaves; ++w) all += w_mass[w];
     W = (unsigned long long)ldexp(all, scale);
   }
-  if (!have_k && (cut_k || top_p < 1.f)) {
+  if (gather) {
     unsigned long long near = 0;
     uint32_t over = 0;
     for (int w = 0; w < kWarpWaves; ++w) {
@@ -630,16 +656,29 @@ void warp_kernel(int V, const float* __restrict__ logits, float inv_t, int greed
   }
 
   if (top_p < 1.f && !have_p) {
-    unsigned long long target = (unsigned long long)ceil((double)top_p * (double)W);
-    target = target < 1 ? 1 : (target > W ? W : target);
+    unsigned long long target = 0;
+    auto set_target = [&]() {
+      target = (unsigned long long)ceil((double)top_p * (double)W);
+      target = target < 1 ? 1 : (target > W ? W : target);
+    };
+    set_target();
     uint32_t prefix = 0;
     unsigned long long above = 0;
+    bool tied = false;
     if (!among && whole) {
       // The cut lies below the kept entries (a flat row), or too many were
-      // kept: one pass histograms the row's mass over 2048 bins of 1/64 nat from
-      // the maximum, another keeps the entries of the bin where the running
-      // mass reaches the target.
-      auto bin_of = [&](float xv) { return (int)min((m - xv) * inv_t * 64.f, (float)(kBuckets - 1)); };
+      // kept: one pass histograms the row's mass over 2048 bins from the
+      // maximum, another keeps the entries of the bin where the running mass
+      // reaches the target.  Bins of 1/64 nat; in rows whose maxima lie within
+      // two nats, where atomics would meet in few of those and one hold too many
+      // entries, 1024 over eight times the maxima's spread and then of 1/32.
+      const bool fine = spread > 0.f && spread < 2.f;
+      const float per = fine ? fminf(128.f / spread, 1e30f) : 64.f;
+      const float far = fine ? 32.f : 0.f, far0 = fine ? 1024.f - 256.f * spread : kBuckets - 1.f;
+      auto bin_of = [&](float xv) {
+        const float d = (m - xv) * inv_t;
+        return (int)fminf(fminf(d * per, fmaf(d, far, far0)), kBuckets - 1.f);
+      };
       for (int i = tid; i < kBuckets; i += kWarpThreads) {
         hmass[i] = 0;
         hcnt[i] = 0;
@@ -650,10 +689,18 @@ void warp_kernel(int V, const float* __restrict__ logits, float inv_t, int greed
         if (w != 0) atomicAdd(&hmass[kBuckets - 1 - bin_of(xv)], w);  // far entries would meet in one bin
       });
       __syncthreads();
+      if (flat) {  // no pass has summed the row yet
+        unsigned long long all = 0;
+        for (int i = lane; i < kBuckets; i += kWave) all += hmass[i];
+        for (int off = 32; off >= 1; off >>= 1) all += shfl_xor_u64(all, off);
+        W = all;
+        set_target();
+      }
       if (wave == 0) select_bucket<true>(hcnt, hmass, kBuckets, target, &s_bucket, &s_cnt_above, &s_mass_above);
       __syncthreads();
       const int bin = kBuckets - 1 - (int)s_bucket;
-      const unsigned long long bin_above = s_mass_above;
+      const unsigned long long bin_above = s_mass_above, bin_mass = hmass[s_bucket];
+      __syncthreads();
       for (int i = tid; i < kBuckets; i += kWarpThreads) hmass[i] = 0;
       mine = 0;
       uint32_t lo = 0xffffffffu, hi = 0;
@@ -687,7 +734,11 @@ void warp_kernel(int V, const float* __restrict__ logits, float inv_t, int greed
       }
       // Masses summed in 64-bit integers here and in float64 in W may put the
       // target a rounding past the last bin: the radix descent handles that too.
-      if (full == 0 && kbase <= kmax && target > bin_above) {
+      if (kbase == kmax && target > bin_above && target <= bin_above + bin_mass) {
+        tied = true;  // every entry of the bin: the cut is their key
+        prefix = kbase;
+        W = bin_above + bin_mass;
+      } else if (full == 0 && kbase <= kmax && target > bin_above) {
         among = true;
         above = bin_above;
       }
@@ -698,7 +749,7 @@ void warp_kernel(int V, const float* __restrict__ logits, float inv_t, int greed
       W += above;
       above = 0;
     }
-    for (int level = 0; level < 3 && !among; ++level) {
+    for (int level = 0; level < 3 && !among && !tied; ++level) {
       const Level lv = level_of(level);
       histogram(level, lv, prefix, theta);
       if (wave == 0)
@@ -727,13 +778,20 @@ hipError_t launch_warp(int M, int V, const float* logits, float temperature, int
                        float* row_lse, float* row_min_logit, hipStream_t stream, hipEvent_t ev_start, const float2* partials,
                        int ntiles, int tile_n) {
   if (M <= 0) return hipSuccess;
-  const int greedy = temperature == 0.f;
+  const bool greedy = temperature == 0.f;
   const float inv_t = greedy ? 0.f : 1.f / temperature;  // float32 division, correctly rounded
   int bits = 0;
   while ((int64_t(1) << bits) < V) ++bits;
   const int scale = 62 - bits;
-  hipExtLaunchKernelGGL(warp_kernel, dim3(M), dim3(kWarpThreads), 0, stream, ev_start, nullptr, 0, V, logits, inv_t,
-                        greedy, top_k, top_p, scale, partials, ntiles, tile_n, out, row_lse, row_min_logit);
+  const bool cut_k = top_k >= 1 && top_k < V;
+  const Cut cut = greedy ? kGreedy : (!cut_k ? kNoK : (top_k <= kWave ? kSmallK : kLargeK));
+  const bool tiles = partials != nullptr;
+  const auto kern = cut == kGreedy   ? (tiles ? warp_kernel<kGreedy, true> : warp_kernel<kGreedy, false>)
+                    : cut == kSmallK ? (tiles ? warp_kernel<kSmallK, true> : warp_kernel<kSmallK, false>)
+                    : cut == kLargeK ? (tiles ? warp_kernel<kLargeK, true> : warp_kernel<kLargeK, false>)
+                                     : (tiles ? warp_kernel<kNoK, true> : warp_kernel<kNoK, false>);
+  hipExtLaunchKernelGGL(kern, dim3(M), dim3(kWarpThreads), 0, stream, ev_start, nullptr, 0, V, logits, inv_t, top_k,
+                        top_p, scale, partials, ntiles, tile_n, out, row_lse, row_min_logit);
   return hipGetLastError();
 }
 

@@ -261,3 +261,46 @@ def test_masked_logits_carry_no_mass(V, T, k, p):
                                   f(B, G, dt=torch.int32), f(B, dt=torch.int32),
                                   torch.empty(sd.sd_workspace_bytes(dims, 100), dtype=torch.uint8, device="cuda"))
     _check_cut(x, T, k, p, to_np(lse), to_np(mn))
+
+
+def _odd_rows(kind, V, rng):
+    x = rng.standard_normal((3, V)).astype(np.float32)
+    if kind == "flat":  # within a nat of each other
+        x *= 0.05
+    elif kind == "nats":  # within a few
+        x *= 0.5
+    elif kind == "equal":
+        x[:] = np.float32(1.25)
+    elif kind == "tied":  # a few values, each held by many entries
+        x = np.rint(x)
+    elif kind == "steps":  # few high ones alike in every thread's share, the others far below
+        x = np.where(np.arange(V) % 37 == 0, x * np.float32(0.01), x * np.float32(0.3) - 9).astype(np.float32)
+    elif kind == "few":  # fewer unmasked entries than a top-k
+        x[:, rng.permutation(V)[30:]] = -np.inf
+        x[1, np.isinf(x[1])] = np.finfo(np.float32).min
+    return x
+
+
+@pytest.mark.parametrize("V", [90, 3001, 40000, 128257])
+@pytest.mark.parametrize("kind", ["flat", "nats", "equal", "tied", "steps", "few"])
+def test_cut_of_rows_unlike_normal_ones(kind, V):
+    """Rows whose cut is not among the few thousand largest entries: histogram
+    bins by the row's spread, a bin of one value that no list holds, top-k past
+    what is kept, fewer unmasked entries than top-k.  Cut and log-sum-exp as the
+    oracle's."""
+    rng = np.random.default_rng(V * 7 + len(kind))
+    x = _odd_rows(kind, V, rng)
+    B, G = 1, 3
+    dims = sd.Dims.of(get_config("tiny").replace(batch=B, gamma=G - 1, vocab=V))
+    f = lambda *s, dt=torch.float32: torch.full(s, -7, dtype=dt, device="cuda")  # noqa: E731
+    for T, k, p in [(1.0, 0, 0.9), (1.0, 0, 0.2), (0.7, 0, 0.999), (3.0, 0, 0.5), (1.0, 40, 0.9), (1.0, 900, 0.95),
+                    (0.8, V - 40, 0.95), (1.0, 0, 1.0)]:
+        announce(f"odd rows kind={kind} V={V} T={T} k={k} p={p}")
+        lse, mn = f(B * G), f(B * G)
+        sd.sd_accept_resample_sampled(dims, sd.Sampling(T, k, p), torch.from_numpy(x).cuda(),
+                                      torch.full((B, G - 1, V), 1.0 / V, device="cuda"),
+                                      f(B, G - 1, dt=torch.int32).zero_(), f(B, G).fill_(0.5), np.full(B, 100, np.int32),
+                                      lse, mn, f(B, dt=torch.int32), f(B, G, dt=torch.int32), f(B, dt=torch.int32),
+                                      torch.empty(sd.sd_workspace_bytes(dims, 100), dtype=torch.uint8, device="cuda"))
+        for r in range(B * G):  # row by row: one row near a cumulative mass may differ
+            _check_cut(x[r:r + 1], T, k, p, to_np(lse)[r:r + 1], to_np(mn)[r:r + 1])
