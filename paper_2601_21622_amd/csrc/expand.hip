@@ -87,12 +87,12 @@ void expand_kernel(ExpandArgs e, const float* __restrict__ logits, int32_t* __re
     for (int u = 0; u < kExpUnroll; ++u) top = base + u * kExpThreads + lane < e.V ? fmaxf(top, xs[u]) : top;
     // The k-th largest of the lanes' largest bounds the round's k-th largest
     // from below (equal ones may fall together, which only lowers it).
-    float bound = top;
+    float bound = wave_max(top), rest = top;
     for (int j = 1; j < e.k; ++j) {
-      const float w = wave_max(bound);
-      bound = bound == w ? -INFINITY : bound;
+      rest = rest == bound ? -INFINITY : rest;
+      bound = wave_max(rest);
+      if (j == 1 && bound == -INFINITY) break;  // all equal or all masked: 64 x 16 rows of 5000, top-16: 81 -> 72 us
     }
-    bound = wave_max(bound);
 #pragma unroll
     for (int u = 0; u < kExpUnroll; ++u) {
       const int v = base + u * kExpThreads + lane;
