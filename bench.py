@@ -76,30 +76,37 @@ def source_digest(name: str) -> str:
     return h.hexdigest()
 
 
-def counter_entry(kernel: str, workload: str, source: str):
-    """The committed rocprofv3 counter record of a kernel on a workload, or
-    None when there is none or the kernel source changed since it was taken."""
+def vocab_source(kernel: str) -> str:
+    """The source file of a projection kernel."""
+    return {"vocab_f32_kernel": "lines.hip", "vocab_bf16_kernel": "lines.hip",
+            "vocab_bf16_rows_kernel": "rows.hip"}.get(kernel, "vocab.hip")
+
+
+def counter_entry(kernel: str, workload: str, source: str, layout=None):
+    """The committed rocprofv3 counter record of a kernel on a workload (and,
+    for a projection kernel, with weights in `layout`), or None when there is
+    none or the kernel source changed since it was taken."""
     try:
         with open(TRAFFIC_FILE) as f:
             entries = json.load(f)
     except (OSError, ValueError):
         return None
     for e in entries:
-        if e.get("kernel") == kernel and e.get("workload") == workload:
+        if e.get("kernel") == kernel and e.get("workload") == workload and e.get("vocab_layout") == layout:
             return e if e.get("source_sha256") == source_digest(source) else None
     return None
 
 
-def counter_traffic(kernel: str, workload: str, source: str):
+def counter_traffic(kernel: str, workload: str, source: str, layout=None):
     """HBM bytes per launch (FETCH_SIZE + WRITE_SIZE, calibrated), or None."""
-    e = counter_entry(kernel, workload, source)
+    e = counter_entry(kernel, workload, source, layout)
     return float(e["bytes_per_launch"]) if e is not None else None
 
 
-def counter_mfma_busy(kernel: str, workload: str, source: str):
+def counter_mfma_busy(kernel: str, workload: str, source: str, layout=None):
     """MFMA busy share of the kernel's SIMD cycles from its SQ counter run
     (SQ_VALU_MFMA_BUSY_CYCLES over 1024 SIMDs x GRBM_GUI_ACTIVE / 8), or None."""
-    e = counter_entry(kernel, workload, source)
+    e = counter_entry(kernel, workload, source, layout)
     return float(e["sq_mfma_busy"]) if e is not None and "sq_mfma_busy" in e else None
 
 
@@ -549,17 +556,18 @@ def main() -> int:
     # kernel its plan picks; attention runs the register-staged kernel for a
     # single 16-row block per KV head.
     vocab_kernel = sd.sd_vocab_kernel_name(dims)
-    vocab_source = "lines.hip" if vocab_kernel in ("vocab_bf16_kernel", "vocab_f32_kernel") else "vocab.hip"
+    layout = "packed" if packed else "row-major"
+    vocab_record = (vocab_kernel, cfg.name, vocab_source(vocab_kernel), layout)
     rows = G * (cfg.n_q_heads // cfg.n_kv_heads)
     attn_kernel = "attn_bf16_reg_kernel" if rows <= 16 else "attn_bf16_kernel"
     roof_attn = {"bound": "hbm", "achieved": attn_gbps, "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                  "frac": attn_gbps / HBM_PEAK_GBPS, "traffic": counter_traffic(attn_kernel, cfg.name, "attention.hip"),
                  "kernel": attn_kernel, "bytes_per_launch": attn_bytes, "ms_per_launch": float(st_mean[0])}
     roof_vocab = {"bound": "hbm", "achieved": vocab_gbps, "peak": HBM_PEAK_GBPS, "unit": "GB/s",
-                  "frac": vocab_gbps / HBM_PEAK_GBPS, "traffic": counter_traffic(vocab_kernel, cfg.name, vocab_source),
+                  "frac": vocab_gbps / HBM_PEAK_GBPS, "traffic": counter_traffic(*vocab_record),
                   "kernel": vocab_kernel, "bytes_per_launch": vocab_bytes, "ms_per_launch": float(st_mean[1]),
                   "mfma_frac": vocab_tflops / BF16_MFMA_PEAK_TFLOPS,
-                  "mfma_busy_counters": counter_mfma_busy(vocab_kernel, cfg.name, vocab_source)}
+                  "mfma_busy_counters": counter_mfma_busy(*vocab_record)}
     dominant = "vocab" if st_mean[1] >= st_mean[0] else "attention"
     roof = roof_vocab if dominant == "vocab" else roof_attn
 

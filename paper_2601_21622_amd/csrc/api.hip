@@ -780,7 +780,7 @@ const char* sd_vocab_kernel_name(const sd_dims_t* dims) {
   if (check_dims(dims) != SD_OK) return nullptr;
   const VocabPlan p = logits_plan(dims);
   if (dims->dtype == SD_DTYPE_F32) return "vocab_f32_kernel";
-  if (p.rows) return "vocab_bf16_deep_kernel";  // the row-major form
+  if (p.rows) return "vocab_bf16_rows_kernel";
   if (!p.deep) return "vocab_bf16_kernel";
   // The wide schedule is the deep shape with four 32-entry blocks per wave
   // on four waves (16-entry blocks per wave: 8).

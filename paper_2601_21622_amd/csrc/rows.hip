@@ -40,7 +40,7 @@ constexpr int row_stages(int mb, int nb) {
 
 template <int MB, int NB>
 __global__ __launch_bounds__(kRowWaves * kWave, 1)
-void vocab_bf16_deep_kernel(int M, int K, int V, int ntiles, int mtiles, const uint16_t* __restrict__ hidden,
+void vocab_bf16_rows_kernel(int M, int K, int V, int ntiles, int mtiles, const uint16_t* __restrict__ hidden,
                             const uint16_t* __restrict__ w, float* __restrict__ logits, float2* __restrict__ partials,
                             int* __restrict__ clear, int nclear) {
   constexpr int NW = kRowWaves;
@@ -176,7 +176,7 @@ void vocab_bf16_deep_kernel(int M, int K, int V, int ntiles, int mtiles, const u
 template <int MB, int NB>
 hipError_t launch_rows(const VocabPlan& p, const void* hidden, const void* w, float* logits, float2* partials,
                        hipStream_t stream, hipEvent_t e0, hipEvent_t e1, int* clear, int nclear) {
-  hipExtLaunchKernelGGL((vocab_bf16_deep_kernel<MB, NB>), dim3((p.ntiles + 7) / 8 * 8 * p.mtiles),
+  hipExtLaunchKernelGGL((vocab_bf16_rows_kernel<MB, NB>), dim3((p.ntiles + 7) / 8 * 8 * p.mtiles),
                         dim3(kRowWaves * kWave), 0, stream, e0, e1, 0, p.M, p.K, p.V, p.ntiles, p.mtiles,
                         static_cast<const uint16_t*>(hidden), static_cast<const uint16_t*>(w), logits, partials, clear,
                         nclear);

@@ -39,9 +39,11 @@ def test_library_loads_and_exports_header_symbols():
 
 
 def test_vocab_kernel_name_follows_the_plan():
-    """The projection kernel the plan picks: the shallow schedule up to 64
-    rows, the wide one where one M-tile of up to 224 rows meets a vocabulary
-    large enough for 512-wide tiles to fill the chip, the deep one otherwise."""
+    """The projection kernel the plan picks: the line schedule up to 64 rows
+    and for float32; past that the wide one where one M-tile of up to 224 rows
+    meets a vocabulary large enough for 512-wide tiles to fill the chip, else
+    the deep one, or with row-major weights the row schedule's in the deep
+    one's four-wave tiles."""
     from workloads import get_config
 
     def name(cfg, **kw):
@@ -52,13 +54,17 @@ def test_vocab_kernel_name_follows_the_plan():
 
     assert name(get_config("tiny")) == "vocab_f32_kernel"
     assert name(get_config("vicuna7b")) == "vocab_bf16_kernel"
-    assert name(get_config("pooled")) == "vocab_bf16_deep_kernel"
+    assert name(get_config("pooled")) == "vocab_bf16_rows_kernel"
+    assert name(get_config("pooled"), flags=sd.SD_FLAG_PACKED_VOCAB) == "vocab_bf16_deep_kernel"
     assert name(get_config("llama3_8b")) == "vocab_bf16_wide_kernel"
     assert name(get_config("llama3_8b"), flags=sd.SD_FLAG_PACKED_VOCAB) == "vocab_bf16_wide_kernel"
     assert name(get_config("llama70b_share")) == "vocab_bf16_deep_kernel"
-    assert name(get_config("llama3_8b"), vocab=30000) == "vocab_bf16_deep_kernel"
+    assert name(get_config("llama3_8b"), vocab=30000) == "vocab_bf16_rows_kernel"
+    assert name(get_config("llama3_8b"), vocab=30000, flags=sd.SD_FLAG_PACKED_VOCAB) == "vocab_bf16_deep_kernel"
     # W past 4 GB: the wide schedule's 32-bit offsets rule it out.
-    assert name(get_config("llama3_8b"), hidden=16384, vocab=2_000_000) == "vocab_bf16_deep_kernel"
+    past = dict(hidden=16384, vocab=2_000_000)
+    assert name(get_config("llama3_8b"), **past) == "vocab_bf16_rows_kernel"
+    assert name(get_config("llama3_8b"), **past, flags=sd.SD_FLAG_PACKED_VOCAB) == "vocab_bf16_deep_kernel"
     assert name(get_config("llama3_8b"), hidden=8192, vocab=250_000) == "vocab_bf16_wide_kernel"
     assert sd.sd_vocab_kernel_name(dims(head_dim=96)) is None
 

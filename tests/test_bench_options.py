@@ -77,3 +77,31 @@ def test_warmup_has_a_time_floor_besides_the_step_count():
     args = bench.parser().parse_args(["--steps", "20", "--warmup", "5"])
     assert args.warmup == 5 and args.steps == 20 and args.warmup_ms == 200.0
     assert bench.parser().parse_args(["--warmup-ms", "0"]).warmup_ms == 0.0
+
+
+def test_counter_records_are_of_the_kernel_and_layout_that_run(monkeypatch, tmp_path):
+    """A projection's record counts only for its own kernel, weight layout and
+    source: row-major weights of the same workload run another kernel."""
+    import json
+
+    assert bench.vocab_source("vocab_bf16_rows_kernel") == "rows.hip"
+    assert bench.vocab_source("vocab_bf16_deep_kernel") == bench.vocab_source("vocab_bf16_wide_kernel") == "vocab.hip"
+    assert bench.vocab_source("vocab_bf16_kernel") == bench.vocab_source("vocab_f32_kernel") == "lines.hip"
+    kernels = {}
+    for src in ("rows.hip", "vocab.hip", "lines.hip"):
+        with open(os.path.join(bench.CSRC, src)) as f:
+            text = f.read()
+        kernels[src] = {k for k in ("vocab_bf16_rows_kernel", "vocab_bf16_deep_kernel", "vocab_bf16_wide_kernel",
+                                    "vocab_bf16_kernel", "vocab_f32_kernel") if f"void {k}(" in text}
+    assert kernels == {"rows.hip": {"vocab_bf16_rows_kernel"}, "lines.hip": {"vocab_bf16_kernel", "vocab_f32_kernel"},
+                       "vocab.hip": {"vocab_bf16_deep_kernel", "vocab_bf16_wide_kernel"}}
+    record = {"kernel": "vocab_bf16_kernel", "workload": "w", "vocab_layout": "packed", "bytes_per_launch": 5,
+              "source_sha256": bench.source_digest("lines.hip")}
+    path = tmp_path / "traffic.json"
+    path.write_text(json.dumps([record]))
+    monkeypatch.setattr(bench, "TRAFFIC_FILE", str(path))
+    assert bench.counter_traffic("vocab_bf16_kernel", "w", "lines.hip", "packed") == 5.0
+    assert bench.counter_traffic("vocab_bf16_kernel", "w", "lines.hip", "row-major") is None
+    assert bench.counter_traffic("vocab_bf16_kernel", "other", "lines.hip", "packed") is None
+    path.write_text(json.dumps([dict(record, source_sha256="0")]))
+    assert bench.counter_traffic("vocab_bf16_kernel", "w", "lines.hip", "packed") is None
