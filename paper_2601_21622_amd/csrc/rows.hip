@@ -203,12 +203,12 @@ hipError_t launch_vocab_rows(const VocabPlan& p, const void* hidden, const void*
   case B: return launch_rows<B, N>(p, hidden, w, logits, partials, stream, e0, e1, clear, nclear);
   if (p.nbw == 4) {
     switch (p.mblocks) {
-      SDV_R(2, 2) SDV_R(3, 2) SDV_R(4, 2) SDV_R(5, 2)
+      SDV_R(3, 2) SDV_R(4, 2) SDV_R(5, 2)
       default: return hipErrorInvalidValue;
     }
   }
   switch (p.mblocks) {
-    SDV_R(2, 1) SDV_R(3, 1) SDV_R(4, 1) SDV_R(5, 1) SDV_R(6, 1) SDV_R(7, 1) SDV_R(8, 1)
+    SDV_R(3, 1) SDV_R(4, 1) SDV_R(5, 1) SDV_R(6, 1) SDV_R(7, 1) SDV_R(8, 1)
     default: return hipErrorInvalidValue;
   }
 #undef SDV_R

@@ -22,7 +22,8 @@
 //   * wide (deep rows, large vocabularies): four waves with four blocks of
 //     32 vocabulary entries each, a 512-wide tile whose accumulators fill
 //     both register files; W and hidden both go to LDS by buffer DMA.
-//   * row (row-major W in the deep schedule's four-wave tiles): rows.hip.
+//   * row (row-major W in the deep schedule's four-wave tiles): rows.hip.  The
+//     512-wide tiles read row-major W themselves.
 //     vocab_plan picks, among the deep shapes and the wide one, the one whose
 //     per-CU inflow (W misses plus hidden hits) is smallest.  Workgroups that
 //     share a vocabulary tile (several M-tiles) are dealt to the same XCD.
@@ -636,9 +637,11 @@ hipError_t launch_deep(const VocabPlan& p, const void* w, float* logits, float2*
   if (p.packed)
     hipExtLaunchKernelGGL((vocab_bf16_deep_kernel<MB, NB, S, NW, true>), grid, block, 0, stream, e0, e1, 0, p.M, p.K,
                           p.V, p.ntiles, p.mtiles, hpacked, wv, logits, partials);
-  else
+  else if constexpr (NW == 8)  // four-wave tiles of row-major W are the row schedule's
     hipExtLaunchKernelGGL((vocab_bf16_deep_kernel<MB, NB, S, NW, false>), grid, block, 0, stream, e0, e1, 0, p.M, p.K,
                           p.V, p.ntiles, p.mtiles, hpacked, wv, logits, partials);
+  else
+    return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
@@ -733,8 +736,14 @@ VocabPlan vocab_plan(int dtype, int M, int K, int V, bool packed, bool small) {
         p.mblocks = mb;
       }
     }
-    // Row-major W in tiles that the row schedule has: whole lines there
-    // (320 x 4096 x 32000: 217 us with the deep schedule's loads).
+    // Row-major W: whole lines in the row schedule where it has the tile, in
+    // M-tiles of its own.  Measured there over 65-640 rows x 20,011-60,000 entries
+    // x 4096, 1.2 to 2.4 times as fast as the deep schedule's loads (192 x 50,021:
+    // 246 -> 168 us, 320 x 32,000: 207 -> 111, 448 x 32,000: 224 -> 187).  The tile
+    // stays the packed layout's, so that both give the same log-sum-exps to the
+    // bit; the row schedule's cheaper tile would take 163 us for 384 x 32,000
+    // (176), and for the 512-wide tiles, of which LDS holds no three stages, 350
+    // for 192 x 128,256 (440 with the wide schedule's loads).
     if (!packed && rows_plan(blocks32, &p)) {
       p.rows = true;
       p.deep = false;
@@ -786,11 +795,12 @@ hipError_t launch_vocab(int dtype, const VocabPlan& p, const void* hidden, const
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
+  // An M-tile has three blocks of 32 rows or more: so has the call, and it is
+  // split evenly into tiles of five and more.
 #define SDV_D(B, N, W) \
   case B: return launch_deep<B, N, W>(p, w, logits, partials, hpacked, stream, e0, e1);
   if (p.nbw == 2 * kWideNB) {
     switch (p.mblocks) {
-      case 2: return launch_wide<2>(p, w, logits, partials, hpacked, stream, e0, e1);
       case 3: return launch_wide<3>(p, w, logits, partials, hpacked, stream, e0, e1);
       case 4: return launch_wide<4>(p, w, logits, partials, hpacked, stream, e0, e1);
       case 5: return launch_wide<5>(p, w, logits, partials, hpacked, stream, e0, e1);
@@ -801,18 +811,18 @@ hipError_t launch_vocab(int dtype, const VocabPlan& p, const void* hidden, const
   }
   if (p.waves == 8) {
     switch (p.mblocks) {
-      SDV_D(2, 2, 8) SDV_D(3, 2, 8) SDV_D(4, 2, 8) SDV_D(5, 2, 8)
+      SDV_D(3, 2, 8) SDV_D(4, 2, 8) SDV_D(5, 2, 8)
       default: return hipErrorInvalidValue;
     }
   }
   if (p.nbw == 4) {
     switch (p.mblocks) {
-      SDV_D(2, 2, 4) SDV_D(3, 2, 4) SDV_D(4, 2, 4) SDV_D(5, 2, 4) SDV_D(6, 2, 4) SDV_D(7, 2, 4)
+      SDV_D(3, 2, 4) SDV_D(4, 2, 4) SDV_D(5, 2, 4) SDV_D(6, 2, 4) SDV_D(7, 2, 4)
       default: return hipErrorInvalidValue;
     }
   }
   switch (p.mblocks) {
-    SDV_D(2, 1, 4) SDV_D(3, 1, 4) SDV_D(4, 1, 4) SDV_D(5, 1, 4) SDV_D(6, 1, 4) SDV_D(7, 1, 4) SDV_D(8, 1, 4)
+    SDV_D(3, 1, 4) SDV_D(4, 1, 4) SDV_D(5, 1, 4) SDV_D(6, 1, 4) SDV_D(7, 1, 4) SDV_D(8, 1, 4)
     SDV_D(9, 1, 4) SDV_D(10, 1, 4) SDV_D(11, 1, 4) SDV_D(12, 1, 4)
     default: return hipErrorInvalidValue;
   }
