@@ -1,9 +1,11 @@
 """GPU parity of the row-major projection past 64 rows (whole lines of W and of
-the hidden rows): every row-block count of the 128- and 256-wide tiles with
-partial last blocks, several M-tiles, vocabularies off every tile, K from one
-half line past the pipeline's depth, odd numbers of half lines.  Bound as for
-any float32 sum of K exact products: K * 2^-24 * sum |h||w|; and the packed
-layout, which takes other kernels, gives the same bits."""
+the hidden rows): every row-block count that the 128-wide (three to eight) and
+256-wide (three to five) tiles run with, in one M-tile and in several, partial
+last blocks, vocabularies off every tile, K from one half line past the
+pipeline's depth, odd numbers of half lines; and shapes whose 512-wide tiles
+keep the other schedules.  Bound as for any float32 sum of K exact products:
+K * 2^-24 * sum |h||w|; and the packed layout, which takes other kernels, gives
+the same bits."""
 
 import numpy as np
 import pytest
@@ -18,7 +20,37 @@ pytestmark = pytest.mark.gpu
 # rows (batch, positions), K, V
 CASES = [((13, 5), 32, 40), ((5, 13), 96, 1003), ((19, 5), 64, 257), ((10, 13), 160, 4099), ((32, 5), 288, 20011),
          ((29, 7), 1312, 9001), ((57, 4), 320, 12289), ((51, 5), 96, 33000), ((60, 11), 224, 2049),
-         ((64, 5), 544, 32001), ((40, 3), 1504, 30001), ((128, 7), 416, 5000)]
+         ((64, 5), 544, 32001), ((40, 3), 1504, 30001), ((128, 7), 416, 5000),
+         # 128-wide with six blocks; 256-wide with three to five in one M-tile, three and four in two
+         ((24, 8), 224, 9001), ((12, 8), 96, 60000), ((32, 4), 160, 50000), ((20, 8), 64, 60001), ((24, 8), 224, 50021),
+         ((28, 8), 96, 60000)]
+
+
+def _row_tile(M, V):
+    """Tile width, M-tiles and 32-row blocks per M-tile if the row schedule runs
+    (its tile is the one that the deep shapes' price picks), else None."""
+    blocks, best = -(-M // 32), None
+    for nb, nw, cap in ((1, 4, 12), (2, 4, 7), (2, 8, 5), (4, 4, 7)):
+        mt = -(-blocks // cap)
+        mb = -(-blocks // mt)
+        wgs = -(-V // (32 * nb * nw)) * mt
+        cost = -(-wgs // 256) * ((2.1 + mt - 1) / mt * 32 * nb * nw + 32 * mb)
+        if best is None or cost < best[0]:
+            best = (cost, 32 * nb * nw)
+    if best[1] == 512:
+        return None
+    mt = -(-blocks // {128: 8, 256: 5}[best[1]])
+    return best[1], mt, -(-blocks // mt)
+
+
+def test_cases_cover_every_row_tile():
+    ran = [_row_tile(b * g, V) for (b, g), _, V in CASES]
+    for ((b, g), K, V), tile in zip(CASES, ran):
+        name = sd.sd_vocab_kernel_name(sd.Dims(b, g - 1, 1, 1, 64, K, V, sd.SD_DTYPE_BF16, 0))
+        assert (name == "vocab_bf16_rows_kernel") == (tile is not None), (b * g, V, name)
+    ran = [t for t in ran if t]
+    assert {(t, mb) for t, _, mb in ran} == {(128, n) for n in range(3, 9)} | {(256, n) for n in range(3, 6)}
+    assert {(t, mt > 1) for t, mt, _ in ran} == {(t, many) for t in (128, 256) for many in (False, True)}
 
 
 @pytest.mark.parametrize("rows,K,V", CASES)
