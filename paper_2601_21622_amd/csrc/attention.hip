@@ -628,7 +628,7 @@ void attn_bf16_kernel(const AttnShape s, const AttnBatch bt, const uint16_t* __r
                       const uint16_t* __restrict__ kp, const uint16_t* __restrict__ vp,
                       AttnPartials parts, const PackJob pj) {
   if ((int)blockIdx.x >= pj.block0) {
-    pack_hidden_block(pj, blockIdx.x - pj.block0);
+    pack_hidden_block<kPackEach>(pj, blockIdx.x - pj.block0);
     return;
   }
   using T = Tile<D>;
@@ -752,7 +752,7 @@ void attn_bf16_reg_kernel(const AttnShape s, const AttnBatch bt, const uint16_t*
                           const uint16_t* __restrict__ kp, const uint16_t* __restrict__ vp,
                           AttnPartials parts, const PackJob pj) {
   if ((int)blockIdx.x >= pj.block0) {
-    pack_hidden_block(pj, blockIdx.x - pj.block0);
+    pack_hidden_block<kPackEach>(pj, blockIdx.x - pj.block0);
     return;
   }
   using T = Tile<D>;

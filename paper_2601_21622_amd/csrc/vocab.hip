@@ -599,7 +599,7 @@ void vocab_bf16_wide_kernel(int M, int K, int V, int ntiles, int mtiles, const u
 }
 
 __global__ __launch_bounds__(kPackThreads)
-void pack_hidden_kernel(const PackJob j) { pack_hidden_block(j, blockIdx.x); }
+void pack_hidden_kernel(const PackJob j) { pack_hidden_block<1>(j, blockIdx.x); }
 
 // One wave per row: maximum over tiles, then a float64 sum of the rescaled tile sums.
 __global__ __launch_bounds__(kVThreads)
@@ -764,6 +764,12 @@ size_t vocab_workspace_bytes(const VocabPlan& p) {
   return b;
 }
 
+// Workgroups that repack the hidden rows, `each` pieces per thread.
+static int pack_blocks(const VocabPlan& p, int each) {
+  const int64_t pieces = (int64_t)(p.K / 16) * ((p.M + 31) / 32) * 64;
+  return (int)((pieces + kPackThreads * each - 1) / (kPackThreads * each));
+}
+
 PackJob vocab_pack_job(const VocabPlan& p, const void* hidden, void* workspace, int* clear, int nclear) {
   PackJob j{};
   if (!p.deep) return j;
@@ -773,8 +779,7 @@ PackJob vocab_pack_job(const VocabPlan& p, const void* hidden, void* workspace, 
   j.out = reinterpret_cast<uint16_t*>(static_cast<char*>(workspace) + partial_bytes(p));
   j.clear = clear;
   j.nclear = clear != nullptr ? nclear : 0;
-  const int64_t pieces = (int64_t)(p.K / 16) * ((p.M + 31) / 32) * 64;
-  j.nblocks = (int)((pieces + kPackThreads * kPackEach - 1) / (kPackThreads * kPackEach));
+  j.nblocks = pack_blocks(p, kPackEach);
   return j;
 }
 
@@ -791,7 +796,7 @@ hipError_t launch_vocab(int dtype, const VocabPlan& p, const void* hidden, const
   // launch a kernel trace lists.
   if (!packed_hidden) {
     const PackJob j = vocab_pack_job(p, hidden, workspace, clear, nclear);
-    hipLaunchKernelGGL(pack_hidden_kernel, dim3(j.nblocks), dim3(kPackThreads), 0, stream, j);
+    hipLaunchKernelGGL(pack_hidden_kernel, dim3(pack_blocks(p, 1)), dim3(kPackThreads), 0, stream, j);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
