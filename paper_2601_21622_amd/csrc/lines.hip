@@ -17,6 +17,11 @@
 // one LDS-only barrier per step (the hidden lines are shared).  Two workgroups
 // share a CU where their stages fit: one's start and epilogue run under the
 // other's stream (52 x 1536 x 50021: 45.6 us with one, 39.7 with two).
+// bfloat16 reads a line's fragments a step ahead, since with one workgroup per
+// CU or none a step is a chain of barrier, reads and products (with the lse
+// launch, packed: 64 x 4096 x 4000 41.6 -> 29.6 us, 20 x 1024 x 5003 12.9 ->
+// 11.3, large vocabularies alike); float32, bound by its products, reads them in
+// the step itself (40 x 1024 x 32000: 43.6 us, 54.3 a step ahead).
 //
 // Bound by HBM (W is read once) at bfloat16: 48 x 4096 x 32000 packed takes 44
 // us, 6.1 TB/s.  float32 at 40 x 1024 x 32000 takes 40 us where scalar FMAs on
@@ -26,6 +31,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "common.h"
 #include "launch.h"
@@ -94,7 +100,7 @@ __device__ __forceinline__ void vocab_lines(int M, int K, int V, int ntiles, int
   constexpr int kHd = (kHBlocks + NW - 1) / NW;  // of which wave w brings w, w + NW, ...
   constexpr int kStage = (kHBlocks + 2 * NW) * 1024;
   constexpr int S = line_stages(kStage);
-  static_assert(S >= 3 && (S - 2) * (2 + kHd) < 64, "vmcnt holds 6 bits");
+  static_assert(S >= 3 && (S - 1) * (2 + kHd) < 64, "vmcnt holds 6 bits");
   __shared__ __align__(1024) unsigned char lds[S * kStage];
   __shared__ float red[NW][16 * MB];
 
@@ -171,35 +177,74 @@ __device__ __forceinline__ void vocab_lines(int M, int K, int V, int ntiles, int
   for (int mb = 0; mb < MB; ++mb) acc[mb][0] = acc[mb][1] = f32x4{0.f, 0.f, 0.f, 0.f};
   const int rd0 = line_read(lane, 0), rd1 = line_read(lane, 1);
 
+  struct Frags {
+    u32x4 w[2], h[MB][2];
+  };
+  auto read = [&](int s, Frags& f) {
+    const unsigned char* src = lds + s * kStage;
+    const unsigned char* wsl = src + (kHBlocks + 2 * wave) * 1024;
+    f.w[0] = *reinterpret_cast<const u32x4*>(wsl + (PACKED ? lane * 16 : rd0));
+    f.w[1] = *reinterpret_cast<const u32x4*>(wsl + (PACKED ? 1024 + lane * 16 : rd1));
 #pragma unroll
-  for (int c = 0; c < S - 1; ++c)
-    if (c < nlines) issue(c, c);
-  int s = 0;
-  for (int c = 0; c < nlines; ++c) {
-    // Until step c has landed: in the steady state S - 2 later steps stay in
-    // flight; the last S - 2 steps wait for everything.
-    if (nlines - 1 - c > S - 2) {
+    for (int mb = 0; mb < MB; ++mb) {
+      f.h[mb][0] = *reinterpret_cast<const u32x4*>(src + mb * 2048 + rd0);
+      f.h[mb][1] = *reinterpret_cast<const u32x4*>(src + mb * 2048 + rd1);
+    }
+  };
+  // Until all but the newest N steps' lines have landed; `all` of them
+  // where fewer are in flight (the last steps of a row).
+  auto wait = [&](auto steps, bool all) {
+    constexpr int N = decltype(steps)::value;
+    if (!all) {
       if (nh == kHd)
-        wait_vmcnt<(S - 2) * (2 + kHd)>();
+        wait_vmcnt<N * (2 + kHd)>();
       else
-        wait_vmcnt<(S - 2) * (1 + kHd)>();
+        wait_vmcnt<N * (1 + kHd)>();
     } else {
       wait_vmcnt<0>();
     }
-    lds_barrier();  // every wave's lines of step c are in, and the stage before has been read
-    if (c + S - 1 < nlines) issue(s == 0 ? S - 1 : s - 1, c + S - 1);
-    const unsigned char* src = lds + s * kStage;
-    const unsigned char* wsl = src + (kHBlocks + 2 * wave) * 1024;
-    const u32x4 wf[2] = {*reinterpret_cast<const u32x4*>(wsl + (PACKED ? lane * 16 : rd0)),
-                         *reinterpret_cast<const u32x4*>(wsl + (PACKED ? 1024 + lane * 16 : rd1))};
-    u32x4 hf[MB][2];
+  };
+  auto halves = [&](int c) { return c == nlines - 1 ? tail : 2; };  // tail is 2 where steps wrap around
+  if constexpr (sizeof(T) == 2) {
+    // A step reads the next line's fragments while it multiplies its own, and
+    // then has its stage filled again: the DMAs issue under the reads' latency.
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-      hf[mb][0] = *reinterpret_cast<const u32x4*>(src + mb * 2048 + rd0);
-      hf[mb][1] = *reinterpret_cast<const u32x4*>(src + mb * 2048 + rd1);
+    for (int c = 0; c < S; ++c)
+      if (c < nlines) issue(c, c);
+    wait(std::integral_constant<int, S - 1>{}, nlines < S);
+    lds_barrier();
+    Frags f0, f1;
+    read(0, f0);
+    int s = 0;
+    auto step = [&](int c, const Frags& now, Frags& next) {
+      if (c + 1 < nlines) {
+        wait(std::integral_constant<int, S - 2>{}, c + S - 1 >= nlines);
+        lds_barrier();  // every wave's lines of step c + 1 are in, and those of step c have been read
+        const int sn = s + 1 == S ? 0 : s + 1;
+        read(sn, next);
+        if (c + S < nlines) issue(s, c + S);
+        s = sn;
+      }
+      line_mma<MB>(hidden, now.w, now.h, acc, halves(c));
+    };
+    for (int c = 0; c < nlines; c += 2) {
+      step(c, f0, f1);
+      if (c + 1 < nlines) step(c + 1, f1, f0);
     }
-    line_mma<MB>(hidden, wf, hf, acc, c == nlines - 1 ? tail : 2);  // tail is 2 where steps wrap around
-    s = s + 1 == S ? 0 : s + 1;
+  } else {
+#pragma unroll
+    for (int c = 0; c < S - 1; ++c)
+      if (c < nlines) issue(c, c);
+    int s = 0;
+    for (int c = 0; c < nlines; ++c) {
+      wait(std::integral_constant<int, S - 2>{}, nlines - 1 - c <= S - 2);
+      lds_barrier();  // every wave's lines of step c are in, and the stage before has been read
+      if (c + S - 1 < nlines) issue(s == 0 ? S - 1 : s - 1, c + S - 1);
+      Frags f;
+      read(s, f);
+      line_mma<MB>(hidden, f.w, f.h, acc, halves(c));
+      s = s + 1 == S ? 0 : s + 1;
+    }
   }
   f32x4 sum[MB][1];
 #pragma unroll
