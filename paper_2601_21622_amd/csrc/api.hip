@@ -89,10 +89,6 @@ size_t attention_ws(const sd_dims_t* d, int64_t chunks) {
   return align_up(attn_partial_bytes(chunks, s.Hkv, s.rows, s.D));
 }
 
-// Tree verification: reserved at the start of the workspace (8 bytes per
-// position; the kernels derive the ancestor masks themselves).
-size_t tree_ws(const sd_dims_t* d) { return align_up(sizeof(uint64_t) * static_cast<size_t>(d->batch) * (d->gamma + 1)); }
-
 // The projection's plan; `small`: the one whose statistics take the least
 // workspace, for a caller whose workspace does not hold the other's.
 VocabPlan logits_plan(const sd_dims_t* d, bool small = false) {
@@ -343,7 +339,7 @@ extern "C" {
 size_t sd_workspace_bytes(const sd_dims_t* dims, int32_t max_kv_len) {
   if (check_dims(dims) != SD_OK || max_kv_len < dims->gamma + 1) return 0;
   const int64_t chunks = attn_max_chunks(dims->dtype, dims->n_kv_heads, dims->batch, max_kv_len);
-  return std::max({tree_ws(dims) + attention_ws(dims, chunks) + logits_ws(logits_plan(dims)) + accept_stage_ws(dims),
+  return std::max({attention_ws(dims, chunks) + logits_ws(logits_plan(dims)) + accept_stage_ws(dims),
                    rate_ws(dims)});
 }
 
@@ -379,11 +375,10 @@ int sd_verify_attention_tree(const sd_dims_t* dims, const void* q, const void* k
   st = check_kv(dims, kv_off, kv_len);
   if (st != SD_OK) return st;
   const AttnShape s = attn_shape(dims, scale, kv_len);
-  if (workspace_bytes < tree_ws(dims) + attention_ws(dims, total_chunks(kv_len, dims->batch, s.chunk_keys)))
+  if (workspace_bytes < attention_ws(dims, total_chunks(kv_len, dims->batch, s.chunk_keys)))
     return SD_ERR_WORKSPACE;
-  return run_attention(dims, q, k_pool, v_pool, kv_off, kv_len, scale, out,
-                       static_cast<char*>(workspace) + tree_ws(dims), static_cast<hipStream_t>(stream), nullptr,
-                       nullptr, parent);
+  return run_attention(dims, q, k_pool, v_pool, kv_off, kv_len, scale, out, workspace,
+                       static_cast<hipStream_t>(stream), nullptr, nullptr, parent);
 }
 
 int sd_verify_logits(const sd_dims_t* dims, const void* hidden, const void* w_vocab, float* logits,
@@ -646,10 +641,10 @@ int sd_verify_step_tree(const sd_dims_t* dims, const void* q, const void* k_pool
   st = check_kv(dims, kv_off, kv_len);
   if (st != SD_OK) return st;
   const AttnShape s = attn_shape(dims, scale, kv_len);
-  const size_t attn_bytes = tree_ws(dims) + attention_ws(dims, total_chunks(kv_len, dims->batch, s.chunk_keys));
+  const size_t attn_bytes = attention_ws(dims, total_chunks(kv_len, dims->batch, s.chunk_keys));
   // As in the chain step: with the caller's hidden rows the attention merge
   // rides in the acceptance's last launch, and the partials keep their region:
-  // [reserved][partials][projection][acceptance].
+  // [partials][projection][acceptance].
   const bool defer = hidden != nullptr;
   const size_t base = defer ? attn_bytes : 0;
   VocabPlan vp;
@@ -666,9 +661,8 @@ int sd_verify_step_tree(const sd_dims_t* dims, const void* q, const void* k_pool
   int* arrivals = accept_arrivals(acc_ws, dims->batch, dims->vocab);
   const PackJob pack = defer ? vocab_pack_job(vp, hidden, vws, arrivals, dims->batch) : PackJob{};
   std::vector<CombineJob> merges;
-  st = run_attention(dims, q, k_pool, v_pool, kv_off, kv_len, scale, attn_out,
-                     static_cast<char*>(workspace) + tree_ws(dims), stm, ev[0], ev[1], parent, nullptr,
-                     defer ? &merges : nullptr, &pack);
+  st = run_attention(dims, q, k_pool, v_pool, kv_off, kv_len, scale, attn_out, workspace, stm, ev[0], ev[1], parent,
+                     nullptr, defer ? &merges : nullptr, &pack);
   if (st != SD_OK) return st;
   if (launch_vocab(dims->dtype, vp, hidden != nullptr ? hidden : attn_out, w_vocab, logits, vws, stm, ev[2], ev[3],
                    arrivals, dims->batch, pack.nblocks > 0) != hipSuccess)
