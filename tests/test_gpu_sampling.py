@@ -304,3 +304,29 @@ def test_cut_of_rows_unlike_normal_ones(kind, V):
                                       torch.empty(sd.sd_workspace_bytes(dims, 100), dtype=torch.uint8, device="cuda"))
         for r in range(B * G):  # row by row: one row near a cumulative mass may differ
             _check_cut(x[r:r + 1], T, k, p, to_np(lse)[r:r + 1], to_np(mn)[r:r + 1])
+
+
+def test_masses_are_exact_to_two_ulp():
+    """A row of 0 and n entries t, uncut: lse = log(1 + n exp(t)).  The masses'
+    exponential is trusted to two float32 ulp (relative 2^-22); their sum is in
+    float64, and lse is rounded once, half an ulp of it."""
+    V, G = 60000, 64
+    t = np.concatenate([-np.geomspace(1e-3, 11.0, G - 3), [-0.34657359, -2.0794415, -10.0]]).astype(np.float32)
+    n = np.minimum(V - 1, np.ceil(0.4 / np.exp(t.astype(np.float64)))).astype(np.int64)
+    x = np.full((G, V), -np.inf, dtype=np.float32)
+    x[:, 0] = 0.0
+    for r in range(G):
+        x[r, 1:1 + n[r]] = t[r]
+    announce(f"masses, {G} rows of {V}")
+    dims = sd.Dims.of(get_config("tiny").replace(batch=1, gamma=G - 1, n_q_heads=1, n_kv_heads=1, vocab=V))
+    f = lambda *s, dt=torch.float32: torch.full(s, -7, dtype=dt, device="cuda")  # noqa: E731
+    lse, mn = f(G), f(G)
+    sd.sd_accept_resample_sampled(dims, sd.Sampling(1.0, 0, 1.0), torch.from_numpy(x).cuda(),
+                                  torch.full((1, G - 1, V), 1.0 / V, device="cuda"), f(1, G - 1, dt=torch.int32).zero_(),
+                                  f(1, G).fill_(0.5), np.full(1, 100, np.int32), lse, mn, f(1, dt=torch.int32),
+                                  f(1, G, dt=torch.int32), f(1, dt=torch.int32),
+                                  torch.empty(sd.sd_workspace_bytes(dims, 100), dtype=torch.uint8, device="cuda"))
+    w = n * np.exp(t.astype(np.float64))
+    want = np.log1p(w)
+    bound = 0.5 * np.spacing(want.astype(np.float32)).astype(np.float64) + 2.0 ** -22 * w / (1.0 + w)
+    assert np.all(np.abs(to_np(lse).astype(np.float64) - want) <= bound)
