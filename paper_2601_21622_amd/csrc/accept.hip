@@ -20,7 +20,8 @@
 // exceeds u * Z, and writes the emitted tokens and the new cache length.
 // In a whole verification step both run as one launch (accept_fused_kernel):
 // the last workgroup of each request to finish its sums, counted by an
-// arrival counter that the step's vocabulary launch clears, runs the pick.
+// arrival counter that an earlier launch of the step clears (the vocabulary
+// kernel, or the repacking of its hidden rows), runs the pick.
 // p(v) = exp(logit - lse) is evaluated in float64 from the float32 inputs.
 #include <hip/hip_ext.h>
 #include <string.h>
@@ -532,9 +533,8 @@ void accept_pick_kernel(const AcceptArgs a, const AcceptBatch bt, const int32_t*
 // Chain, warped and tree modes in one launch (the verification steps): the
 // sums stage of accept_sums_kernel, after which the last workgroup of each
 // request to finish its segment totals (counted by a per-request arrival
-// counter, which the vocabulary launch that precedes this one in the step
-// clears) draws the request's token on its first wave, as accept_pick_kernel
-// does.
+// counter, which an earlier launch of the step clears) draws the request's token
+// on its first wave, as accept_pick_kernel does.
 // Workgroups past the requests carry an attention merge, two merge blocks
 // each.
 __global__ __launch_bounds__(kSumWaves * kWave, kFusedWgsPerCu * kSumWaves / 4)  // waves per SIMD
