@@ -338,19 +338,29 @@ struct TileLane {
 // registers).  Issued from inline assembly, so the compiler neither tracks it
 // nor inserts waits for it: the kernel's own vmcnt waits order it against the
 // LDS reads.  The load carries the nontemporal hint (every row is read once).
-// Both scalars pass through readfirstlane (free when the compiler already
-// holds them in scalar registers), since the instruction takes them only
-// from scalar registers.  The compiler's hazard pass does not see into the
-// string, so it waits for itself: five states after a readfirstlane that wrote
-// the base (s_mov and s_nop 3), which covers the one after M0's write.
-__device__ __forceinline__ void dma_block(uint32_t lds, const void* gbase, uint32_t voff) {
-  const uint64_t g = (uint64_t)(uintptr_t)gbase;
-  const uint64_t gu = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(g >> 32)) << 32) |
-                      (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)g);
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %2 nt"
+// The instruction takes them only from scalar registers: gbase is uniform_base's
+// or a constant from it, lds passes through readfirstlane (free when the
+// compiler already holds it in one).  The compiler's hazard pass does not see
+// into the string, so it waits the one state that a load into LDS needs after
+// the write of M0 itself.
+__device__ __forceinline__ void dma_block(uint32_t lds, uint64_t gbase, uint32_t voff) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
                :
-               : "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(voff), "s"((const void*)(uintptr_t)gu)
+               : "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(voff), "s"(gbase)
                : "m0", "memory");
+}
+
+// A wave-uniform address in scalar registers, fit for dma_block: five wait states
+// after the readfirstlanes, which the hazard pass would put before its own loads.
+// Once per run of DMAs, whose further bases are scalar sums (with the waits in
+// every DMA, whose base was read into scalar registers for itself, 32 requests of
+// 4096 keys, 7 positions, took 102 us with the merge, 95 so; 31 nodes 137, 134).
+__device__ __forceinline__ uint64_t uniform_base(const void* p) {
+  const uint64_t g = (uint64_t)(uintptr_t)p;
+  uint64_t u = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(g >> 32)) << 32) |
+               (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)g);
+  asm volatile("s_nop 4" : "+s"(u));
+  return u;
 }
 
 // DMA of blocks N0 .. N1-1 of one tile's K (ISV false) or V rows at t into
@@ -359,7 +369,7 @@ template <int D, bool ISV, int N0, int N1>
 __device__ __forceinline__ void dma_tile_part(const uint16_t* t, uint32_t l, const TileLane<D>& tl, int last) {
   using T = Tile<D>;
   const int lane = threadIdx.x & 63;
-  const char* b = reinterpret_cast<const char*>(t);
+  const uint64_t b = uniform_base(t);
   if (last >= kTile - 1) {
 #pragma unroll
     for (int n = N0; n < N1; ++n)
@@ -378,8 +388,7 @@ __device__ __forceinline__ void dma_tile(const uint16_t* kt, const uint16_t* vt,
                                          const TileLane<D>& tl, int last) {
   using T = Tile<D>;
   const int lane = threadIdx.x & 63;
-  const char* kb = reinterpret_cast<const char*>(kt);
-  const char* vb = reinterpret_cast<const char*>(vt);
+  const uint64_t kb = uniform_base(kt), vb = uniform_base(vt);
   if (last >= kTile - 1) {
 #pragma unroll
     for (int n = 0; n < T::kBlocks; ++n) {
