@@ -493,7 +493,7 @@ void warp_kernel(int V, const float* __restrict__ logits, float inv_t, int top_k
   // tile: those of normal rows lie that dense; 40 rows of 32,000, top-k 5000:
   // 50 us tried, 44 not) unless all unmasked entries of a short row fit, and for
   // top_p in rows whose entries lie within a nat, where the largest few hold
-  // too little (0.05 normal, top-p 0.95: 49 us, 40).
+  // too little (0.05 normal, top-p 0.95: 50 us, 37).
   bool among = false;  // the cut is among the kept entries
   int mine = 0;        // this thread's, at s_keep[i * kWarpThreads + tid]
   uint32_t kbase = 0;  // a key no kept entry is below
